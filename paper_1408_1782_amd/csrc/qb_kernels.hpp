@@ -52,13 +52,17 @@ struct DevPlan {
   // work buffers
   T* spec;   // [cells][4][2][P*P]  w_hat_mu, col spec
   T* wP;     // [cells][5][P*P]     w_mu and f0 = 2 w0 - 1 on the P grid, row real
-  T* terms;  // [cells][11][P*P]    I_1 (3), I_4 (4), I_2 (one per Pauli component) real-space fields
-  T* acc;    // [cells][7][2][P*P]  spectral accumulators of the I_1 / I_4 tasks
-  T* i3s;    // [cells][J][4 or 6][P*P]  shifted fields of the current (j, m) (+ partner sums)
-  T* i3o;    // [cells][J][4][P*P]  I_3 partial sums over m, per j
+  T* terms;  // [cells][11][tg][P*P]  I_1 (3), I_4 (4), I_2 (one per Pauli component) real-space fields,
+             //                     one per group of directions (k_terms_vjp: tg = 1)
+  T* acc;    // [cells][7][tg][2][P*P]  spectral accumulators of the I_1 / I_4 tasks
+  // I_3, per task (cell, j, node group)
+  T* i3s;    // [tasks][4 or 6][P*P]  shifted fields of the current (j, m) (+ partner sums)
+  T* i3o;    // [tasks][4][P*P]     sums over the group's nodes m
+  T* i3p;    // [tasks][4][P*P]     partner-node spectra (2 packed pairs, re/im, col spec)
   T* i3sum;  // [cells][4][P*P]     assembled real-space fields of C
-  T* i3p;    // [cells][J][4][P*P]  partner-node spectra of I_3 per j (2 packed pairs, re/im, col spec)
-  T* i3ps;   // [cells][4][P*P]     i3p summed over j
+  T* i3ps;   // [cells][4][P*P]     i3p summed over the cell's tasks
+  int gs, ng;  // node pairs (nodes when unpaired) per group, groups of k_i3
+  int td, tg;  // directions per group, groups of k_terms
   // adjoint work buffers (present once the plan's adjoint is enabled)
   T* lamP;   // [cells][4][P*P]     cotangent of the assembled fields, row real
   T* acot;   // [cells][16][P*P]    assembly cotangents: g (3), y (4), S (1), b (4), w direct (4)
@@ -225,12 +229,9 @@ struct Kern {
   static constexpr int TPR = Eng::TPR;
   static constexpr int FSZ = P * P;
   static constexpr int LDS = Eng::LDS_SCALARS + Eng::TW_SCALARS;
-  // occupancy target of the transform kernels (waves per SIMD): two
-  // workgroups per compute unit where the field is small enough
-#ifndef QB_F32_P128_WAVES
-#define QB_F32_P128_WAVES 1
-#endif
-  static constexpr int WAVES = (sizeof(T) == 4 && P == 128) ? QB_F32_P128_WAVES : 1;
+  // least occupancy of k_i3 (waves per SIMD): two workgroups of 256 threads
+  // per compute unit, which a few registers more than 256 would halve
+  static constexpr int WAVES = 1;
 };
 
 template <typename T, int P, int E, bool XB>
@@ -243,200 +244,7 @@ __device__ __forceinline__ void setup(Fft2<T, P, E, XB>& eng, T* smem, const T* 
   eng.init(smem, t2);
 }
 
-// ------------------------------------------------------------------ dft_in
-// w_mu(v_n) -> w_hat_mu on Xi (Nyquist zeroed, padded to P, col spec), and the
-// trigonometric interpolants w_mu, f0 = 2 w0 - 1 on the P grid (row real).
-template <typename T, int P, int E>
-__global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_dft_in(DevPlan<T> d, const T* __restrict__ w, int cell0) {
-  using K = Kern<T, P, E>;
-  constexpr unsigned S = sizeof(T);
-  __shared__ T smem[K::LDS];
-  Fft2<T, P, E> eng;
-  setup(eng, smem, d.tw);
-  const int cell = cell0 + blockIdx.x;
-  const int N = P / 2;
-  const unsigned vo = threadIdx.x * S;
-  const size_t cs = (size_t)d.Nx * N * N;
-  const int y = eng.line;
-  const rsrc_t rs = mkbuf(d.spec + (size_t)blockIdx.x * 8 * K::FSZ, 8 * K::FSZ);
-  const rsrc_t rw = mkbuf(d.wP + (size_t)blockIdx.x * 5 * K::FSZ, 5 * K::FSZ);
-  const T inv_n2 = (T)1 / (T)(N * N);
-  const int bx = centered<P>(eng.line);
-  const bool kx_in = bx > -N / 2 && bx < N / 2;
-#pragma unroll 1
-  for (int mu = 0; mu < 4; ++mu) {
-    T zr[E], zi[E];
-    // the velocity grid sits on the even points of the padded grid
-    const bool on_grid = ((eng.q | y) & 1) == 0;
-    const T* wrow = w + mu * cs + (size_t)cell * N * N + (centered<P>(y) / 2 + N / 2);
-#pragma unroll
-    for (int n = 0; n < E; ++n) {
-      zr[n] = on_grid ? wrow[vel_index<P, K::TPR>(eng.q, n) * N] : (T)0;
-      zi[n] = 0;
-    }
-    eng.fwd2(zr, zi);
-#pragma unroll
-    for (int k = 0; k < E; ++k) {
-      const int by = centered<P>(eng.bk(k));
-      const bool in = kx_in && by > -N / 2 && by < N / 2;
-      bst<T>(rs, in ? zr[k] * inv_n2 : (T)0, vo, ((2 * mu) * K::FSZ + k * K::NT) * S);
-      bst<T>(rs, in ? zi[k] * inv_n2 : (T)0, vo, ((2 * mu + 1) * K::FSZ + k * K::NT) * S);
-    }
-  }
-#pragma unroll 1
-  for (int pr = 0; pr < 2; ++pr) {
-    T zr[E], zi[E];
-    const unsigned fa = 2 * (2 * pr) * K::FSZ, fb = 2 * (2 * pr + 1) * K::FSZ;
-#pragma unroll
-    for (int k = 0; k < E; ++k) {
-      const unsigned o = k * K::NT;
-      // (a_r + i a_i) + i (b_r + i b_i)
-      zr[k] = bld<T>(rs, vo, (fa + o) * S) - bld<T>(rs, vo, (fb + K::FSZ + o) * S);
-      zi[k] = bld<T>(rs, vo, (fa + K::FSZ + o) * S) + bld<T>(rs, vo, (fb + o) * S);
-    }
-    eng.inv2(zr, zi);
-#pragma unroll
-    for (int n = 0; n < E; ++n) {
-      const unsigned o = n * K::NT;
-      bst<T>(rw, zr[n], vo, ((2 * pr) * K::FSZ + o) * S);
-      bst<T>(rw, zi[n], vo, ((2 * pr + 1) * K::FSZ + o) * S);
-      if (pr == 0) bst<T>(rw, (T)2 * zr[n] - (T)1, vo, (4 * K::FSZ + o) * S);
-    }
-  }
-}
-
-// ------------------------------------------------------------------ I_1, I_4, I_2
-// task 0..2: I_1[f0, w_l, .] (l = task + 1), hoisted outer kernel K_j'
-// task 3..6: I_4[f0, w_g, .] (g = task - 3)
-// Both: sum_j outer_j(p) FFT( f0 * IFFT(inner_j w_hat_g) ), then one IFFT.
-// task 7..10: I_2 accumulator S = sum_mu S_mu, one Pauli component
-//            mu = task - 7 per task: S_mu = sum_j (pi/J) eta_mu
-//            IFFT(psi_j w_hat_mu) IFFT(psi'_j w_hat_mu)   (real space)
-constexpr int kTermPlanes = 11;
-template <typename T, int P, int E>
-__global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_terms(DevPlan<T> d, int ncells) {
-  using K = Kern<T, P, E>;
-  constexpr unsigned S = sizeof(T);
-  __shared__ T smem[K::LDS];
-  Fft2<T, P, E> eng;
-  setup(eng, smem, d.tw);
-  // one (cell, task) per workgroup, or grid-stride when persistent
-#pragma unroll 1
-  for (int pt = blockIdx.x; pt < ncells * kTermPlanes; pt += gridDim.x) {
-  const int cell = pt / kTermPlanes;
-  const int task = pt % kTermPlanes;
-  const unsigned vo = threadIdx.x * S;
-  const rsrc_t rs = mkbuf(d.spec + (size_t)cell * 8 * K::FSZ, 8 * K::FSZ);
-  const rsrc_t rw = mkbuf(d.wP + (size_t)cell * 5 * K::FSZ, 5 * K::FSZ);
-  const rsrc_t ro = mkbuf(d.terms + ((size_t)cell * kTermPlanes + task) * K::FSZ, K::FSZ);
-  const size_t tabn = (size_t)d.J * K::FSZ;
-  if (task < 7) {
-    const int g = task < 3 ? task + 1 : task - 3;
-    const rsrc_t rin = mkbuf(task < 3 ? d.phip : d.psip, tabn);
-    const rsrc_t rout = mkbuf(task < 3 ? d.Kt : d.psiw, tabn);
-    const rsrc_t ra = mkbuf(d.acc + ((size_t)cell * 7 + task) * 2 * K::FSZ, 2 * K::FSZ);
-    const unsigned fg = 2 * g * K::FSZ;
-    // in_j, out_j are real with one parity in k (odd for I_1, even for
-    // I_4) and w_hat_g is the spectrum of a real field, so a_j is real up
-    // to a fixed phase: directions j, j+1 share both transforms, with
-    // coefficients (i_j + i i_j+1, o_j - i o_j+1) for even tables and
-    // (i_j+1 - i i_j, o_j+1 + i o_j) for odd ones.  The real part of the
-    // final inverse transform is the field; the cross terms the sharing
-    // adds are imaginary there.
-    const bool odd = task < 3;
-#pragma unroll 1
-    for (int j = 0; j < d.J; j += 2) {
-      T zr[E], zi[E];
-      const unsigned t1 = j * K::FSZ, t2 = t1 + K::FSZ;
-#pragma unroll
-      for (int k = 0; k < E; ++k) {
-        const unsigned o = k * K::NT;
-        const T i1 = bld<T>(rin, vo, (t1 + o) * S), i2 = bld<T>(rin, vo, (t2 + o) * S);
-        const T cr = odd ? i2 : i1, ci = odd ? -i1 : i2;
-        const T sr = bld<T>(rs, vo, (fg + o) * S), si = bld<T>(rs, vo, (fg + K::FSZ + o) * S);
-        zr[k] = sr * cr - si * ci;
-        zi[k] = sr * ci + si * cr;
-      }
-      eng.inv2(zr, zi);
-#pragma unroll
-      for (int n = 0; n < E; ++n) {
-        const T f = bld<T>(rw, vo, (4 * K::FSZ + n * K::NT) * S);
-        zr[n] *= f;
-        zi[n] *= f;
-      }
-      eng.fwd2(zr, zi);
-#pragma unroll
-      for (int k = 0; k < E; ++k) {
-        const unsigned o = k * K::NT;
-        const T o1 = bld<T>(rout, vo, (t1 + o) * S), o2 = bld<T>(rout, vo, (t2 + o) * S);
-        const T cr = odd ? o2 : o1, ci = odd ? o1 : -o2;
-        T ar = cr * zr[k] - ci * zi[k], ai = cr * zi[k] + ci * zr[k];
-        // read at j = 0 too (not yet written) and dropped by a select
-        const T pr = bld<T>(ra, vo, o * S), pi = bld<T>(ra, vo, (K::FSZ + o) * S);
-        ar += j != 0 ? pr : (T)0;
-        ai += j != 0 ? pi : (T)0;
-        bst<T>(ra, ar, vo, o * S);
-        bst<T>(ra, ai, vo, (K::FSZ + o) * S);
-      }
-    }
-    T zr[E], zi[E];
-#pragma unroll
-    for (int k = 0; k < E; ++k) {
-      const unsigned o = k * K::NT;
-      zr[k] = bld<T>(ra, vo, o * S);
-      zi[k] = bld<T>(ra, vo, (K::FSZ + o) * S);
-    }
-    eng.inv2(zr, zi);
-#pragma unroll
-    for (int n = 0; n < E; ++n) bst<T>(ro, zr[n], vo, (n * K::NT) * S);
-  } else {
-    // one Pauli component per task: S_mu = sum_j e_mu A_j,mu B_j,mu
-    const int mu = task - 7;
-    const unsigned fm = 2 * mu * K::FSZ;
-    const T e = (T)(kPi / d.J) * (mu == 0 ? (T)1 : (T)-1);
-    T Sacc[E];
-#pragma unroll
-    for (int n = 0; n < E; ++n) Sacc[n] = 0;
-    const rsrc_t rps = mkbuf(d.psi, tabn);
-    const rsrc_t rpp = mkbuf(d.psip, tabn);
-#pragma unroll 1
-    for (int j = 0; j < d.J; ++j) {
-      const unsigned tj = j * K::FSZ;
-      T zr[E], zi[E];
-#pragma unroll
-      for (int k = 0; k < E; ++k) {
-        const unsigned o = k * K::NT;
-        const T ar = bld<T>(rs, vo, (fm + o) * S), ai = bld<T>(rs, vo, (fm + K::FSZ + o) * S);
-        const T a = bld<T>(rps, vo, (tj + o) * S), b = bld<T>(rpp, vo, (tj + o) * S);
-        // w_hat psi + i w_hat psi'
-        zr[k] = ar * a - ai * b;
-        zi[k] = ai * a + ar * b;
-      }
-      eng.inv2(zr, zi);
-#pragma unroll
-      for (int n = 0; n < E; ++n) Sacc[n] += e * zr[n] * zi[n];
-    }
-#pragma unroll
-    for (int n = 0; n < E; ++n) bst<T>(ro, Sacc[n], vo, (n * K::NT) * S);
-  }
-  }  // tasks
-}
-
-// ------------------------------------------------------------------ I_3
-// One workgroup per (cell, j); loops over the Gauss-Legendre nodes in
-// symmetric pairs (m, m' = M-1-m), rho_m' = -rho_m, w_m' = w_m (the middle
-// node of an odd M runs alone).  With s_nu = S w_nu the field shifted by
-// node m (S = inv2(exp(i alpha_jm . b) fwd2(.)) / P^2) and the packed
-// convolutions Phi_a,b = Psi(w_a s_b), Psi = inv2(psi'_j / P^2 fwd2(.)):
-//   node m :  o_b  += c sum_a eta_a s_a Phi_a,b                 (real space)
-//   node m':  o'_a  = c S^{-1} sum_b eta_b w_b Phi_a,b
-// because translations commute with Psi and distribute over products whose
-// band stays inside the padded grid; the aliased part of the last product
-// falls outside Xi, which the output keeps.  o' is accumulated as a
-// spectrum, conj(phase) fwd2(sign_a o'_a) with the sign of the B term
-// (-1 for a = 0), packed (0 + i1), (2 + i3), into i3p[cell][j].
-// c = (pi/J) w_m.  Per pair: 2 shift transforms, 8 packed convolutions of 2
-// transforms each, 2 transforms of the partner sums.
+// ------------------------------------------------------------------ register plan
 // Register plan.  One workgroup of NT threads puts NT / 256 waves on each
 // SIMD (at least one), so a thread may hold 512 / that many VGPRs (at most
 // 256).  The working field takes 2 E values; the partner sums of a row pair
@@ -481,7 +289,221 @@ struct I3Regs {
   }
 };
 
-// Planes per (cell, j) of the shifted-field buffer i3s: the four shifted
+// ------------------------------------------------------------------ dft_in
+// w_mu(v_n) -> w_hat_mu on Xi (Nyquist zeroed, padded to P, col spec), and the
+// trigonometric interpolants w_mu, f0 = 2 w0 - 1 on the P grid (row real).
+// One workgroup per (cell, mu): two transforms in sequence, where one per
+// cell runs six; a launch of one cell is bound by that chain (33 -> 14 us at
+// N = 32 in float64), and a launch that fills the chip is too small to matter.
+template <typename T, int P, int E>
+__global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_dft_in(DevPlan<T> d, const T* __restrict__ w, int cell0) {
+  using K = Kern<T, P, E>;
+  constexpr unsigned S = sizeof(T);
+  __shared__ T smem[K::LDS];
+  Fft2<T, P, E> eng;
+  setup(eng, smem, d.tw);
+  const int lc = blockIdx.x >> 2, mu = blockIdx.x & 3;
+  const int cell = cell0 + lc;
+  const int N = P / 2;
+  const unsigned vo = threadIdx.x * S;
+  const size_t cs = (size_t)d.Nx * N * N;
+  const int y = eng.line;
+  const rsrc_t rs = mkbuf(d.spec + (size_t)lc * 8 * K::FSZ, 8 * K::FSZ);
+  const rsrc_t rw = mkbuf(d.wP + (size_t)lc * 5 * K::FSZ, 5 * K::FSZ);
+  const T inv_n2 = (T)1 / (T)(N * N);
+  const int bx = centered<P>(eng.line);
+  const bool kx_in = bx > -N / 2 && bx < N / 2;
+  T zr[E], zi[E];
+  // the velocity grid sits on the even points of the padded grid
+  const bool on_grid = ((eng.q | y) & 1) == 0;
+  const T* wrow = w + mu * cs + (size_t)cell * N * N + (centered<P>(y) / 2 + N / 2);
+#pragma unroll
+  for (int n = 0; n < E; ++n) {
+    zr[n] = on_grid ? wrow[vel_index<P, K::TPR>(eng.q, n) * N] : (T)0;
+    zi[n] = 0;
+  }
+  eng.fwd2(zr, zi);
+#pragma unroll
+  for (int k = 0; k < E; ++k) {
+    const int by = centered<P>(eng.bk(k));
+    const bool in = kx_in && by > -N / 2 && by < N / 2;
+    zr[k] = in ? zr[k] * inv_n2 : (T)0;
+    zi[k] = in ? zi[k] * inv_n2 : (T)0;
+    bst<T>(rs, zr[k], vo, ((2 * mu) * K::FSZ + k * K::NT) * S);
+    bst<T>(rs, zi[k], vo, ((2 * mu + 1) * K::FSZ + k * K::NT) * S);
+  }
+  eng.inv2(zr, zi);
+#pragma unroll
+  for (int n = 0; n < E; ++n) {
+    const unsigned o = n * K::NT;
+    bst<T>(rw, zr[n], vo, (mu * K::FSZ + o) * S);
+    if (mu == 0) bst<T>(rw, (T)2 * zr[n] - (T)1, vo, (4 * K::FSZ + o) * S);
+  }
+}
+
+// ------------------------------------------------------------------ I_1, I_4, I_2
+// task 0..2: I_1[f0, w_l, .] (l = task + 1), hoisted outer kernel K_j'
+// task 3..6: I_4[f0, w_g, .] (g = task - 3)
+// Both: sum_j outer_j(p) FFT( f0 * IFFT(inner_j w_hat_g) ), then one IFFT.
+// task 7..10: I_2 accumulator S = sum_mu S_mu, one Pauli component
+//            mu = task - 7 per task: S_mu = sum_j (pi/J) eta_mu
+//            IFFT(psi_j w_hat_mu) IFFT(psi'_j w_hat_mu)   (real space)
+// Every task is cut into groups of d.td directions, one workgroup each, and
+// k_assemble adds the groups' fields: the chain of transforms in a workgroup
+// is then 9 long whatever J is, against 33 at J = 32 for a whole task (one
+// cell at N = 32 in float64 took 330 us for them), for one final transform
+// more per group.  The spectral accumulators of a group stay in registers
+// where the register plan has room for two more fields (TREG), else they go
+// through the buffer acc.
+constexpr int kTermPlanes = 11;
+template <typename T, int P, int E>
+__global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_terms(DevPlan<T> d, int ncells) {
+  using K = Kern<T, P, E>;
+  constexpr unsigned S = sizeof(T);
+  constexpr bool TREG = I3Regs<T, P, E>::PAIR;
+  __shared__ T smem[K::LDS];
+  Fft2<T, P, E> eng;
+  setup(eng, smem, d.tw);
+  // one (cell, task, group) per workgroup, or grid-stride when persistent
+  const int per_cell = kTermPlanes * d.tg;
+#pragma unroll 1
+  for (int pt = blockIdx.x; pt < ncells * per_cell; pt += gridDim.x) {
+  const int cell = pt / per_cell;
+  const int task = (pt % per_cell) / d.tg;
+  const int grp = pt % d.tg;
+  const int j0 = grp * d.td, j1 = min(d.J, j0 + d.td);
+  const unsigned vo = threadIdx.x * S;
+  const rsrc_t rs = mkbuf(d.spec + (size_t)cell * 8 * K::FSZ, 8 * K::FSZ);
+  const rsrc_t rw = mkbuf(d.wP + (size_t)cell * 5 * K::FSZ, 5 * K::FSZ);
+  const rsrc_t ro = mkbuf(d.terms + (size_t)pt * K::FSZ, K::FSZ);
+  const size_t tabn = (size_t)d.J * K::FSZ;
+  if (task < 7) {
+    const int g = task < 3 ? task + 1 : task - 3;
+    const rsrc_t rin = mkbuf(task < 3 ? d.phip : d.psip, tabn);
+    const rsrc_t rout = mkbuf(task < 3 ? d.Kt : d.psiw, tabn);
+    const rsrc_t ra =
+        mkbuf(TREG ? d.spec : d.acc + (((size_t)cell * 7 + task) * d.tg + grp) * 2 * K::FSZ, 2 * K::FSZ);
+    const unsigned fg = 2 * g * K::FSZ;
+    // in_j, out_j are real with one parity in k (odd for I_1, even for
+    // I_4) and w_hat_g is the spectrum of a real field, so a_j is real up
+    // to a fixed phase: directions j, j+1 share both transforms, with
+    // coefficients (i_j + i i_j+1, o_j - i o_j+1) for even tables and
+    // (i_j+1 - i i_j, o_j+1 + i o_j) for odd ones.  The real part of the
+    // final inverse transform is the field; the cross terms the sharing
+    // adds are imaginary there.
+    const bool odd = task < 3;
+    T sr[TREG ? E : 1], si[TREG ? E : 1];
+    if constexpr (TREG) {
+#pragma unroll
+      for (int k = 0; k < E; ++k) sr[k] = si[k] = 0;
+    }
+#pragma unroll 1
+    for (int j = j0; j < j1; j += 2) {
+      T zr[E], zi[E];
+      const unsigned t1 = j * K::FSZ, t2 = t1 + K::FSZ;
+#pragma unroll
+      for (int k = 0; k < E; ++k) {
+        const unsigned o = k * K::NT;
+        const T i1 = bld<T>(rin, vo, (t1 + o) * S), i2 = bld<T>(rin, vo, (t2 + o) * S);
+        const T cr = odd ? i2 : i1, ci = odd ? -i1 : i2;
+        const T wr = bld<T>(rs, vo, (fg + o) * S), wi = bld<T>(rs, vo, (fg + K::FSZ + o) * S);
+        zr[k] = wr * cr - wi * ci;
+        zi[k] = wr * ci + wi * cr;
+      }
+      eng.inv2(zr, zi);
+#pragma unroll
+      for (int n = 0; n < E; ++n) {
+        const T f = bld<T>(rw, vo, (4 * K::FSZ + n * K::NT) * S);
+        zr[n] *= f;
+        zi[n] *= f;
+      }
+      eng.fwd2(zr, zi);
+#pragma unroll
+      for (int k = 0; k < E; ++k) {
+        const unsigned o = k * K::NT;
+        const T o1 = bld<T>(rout, vo, (t1 + o) * S), o2 = bld<T>(rout, vo, (t2 + o) * S);
+        const T cr = odd ? o2 : o1, ci = odd ? o1 : -o2;
+        const T ar = cr * zr[k] - ci * zi[k], ai = cr * zi[k] + ci * zr[k];
+        if constexpr (TREG) {
+          sr[TREG ? k : 0] += ar;
+          si[TREG ? k : 0] += ai;
+        } else {
+          // read at the first pair too (not yet written) and dropped by a select
+          const T pr = bld<T>(ra, vo, o * S), pi = bld<T>(ra, vo, (K::FSZ + o) * S);
+          bst<T>(ra, ar + (j != j0 ? pr : (T)0), vo, o * S);
+          bst<T>(ra, ai + (j != j0 ? pi : (T)0), vo, (K::FSZ + o) * S);
+        }
+      }
+    }
+    T zr[E], zi[E];
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
+      const unsigned o = k * K::NT;
+      zr[k] = TREG ? sr[TREG ? k : 0] : bld<T>(ra, vo, o * S);
+      zi[k] = TREG ? si[TREG ? k : 0] : bld<T>(ra, vo, (K::FSZ + o) * S);
+    }
+    eng.inv2(zr, zi);
+#pragma unroll
+    for (int n = 0; n < E; ++n) bst<T>(ro, zr[n], vo, (n * K::NT) * S);
+  } else {
+    // one Pauli component per task: S_mu = sum_j e_mu A_j,mu B_j,mu
+    const int mu = task - 7;
+    const unsigned fm = 2 * mu * K::FSZ;
+    const T e = (T)(kPi / d.J) * (mu == 0 ? (T)1 : (T)-1);
+    T Sacc[E];
+#pragma unroll
+    for (int n = 0; n < E; ++n) Sacc[n] = 0;
+    const rsrc_t rps = mkbuf(d.psi, tabn);
+    const rsrc_t rpp = mkbuf(d.psip, tabn);
+#pragma unroll 1
+    for (int j = j0; j < j1; ++j) {
+      const unsigned tj = j * K::FSZ;
+      T zr[E], zi[E];
+#pragma unroll
+      for (int k = 0; k < E; ++k) {
+        const unsigned o = k * K::NT;
+        const T ar = bld<T>(rs, vo, (fm + o) * S), ai = bld<T>(rs, vo, (fm + K::FSZ + o) * S);
+        const T a = bld<T>(rps, vo, (tj + o) * S), b = bld<T>(rpp, vo, (tj + o) * S);
+        // w_hat psi + i w_hat psi'
+        zr[k] = ar * a - ai * b;
+        zi[k] = ai * a + ar * b;
+      }
+      eng.inv2(zr, zi);
+#pragma unroll
+      for (int n = 0; n < E; ++n) Sacc[n] += e * zr[n] * zi[n];
+    }
+#pragma unroll
+    for (int n = 0; n < E; ++n) bst<T>(ro, Sacc[n], vo, (n * K::NT) * S);
+  }
+  }  // tasks
+}
+
+// ------------------------------------------------------------------ I_3
+// One workgroup per (cell, j); loops over the Gauss-Legendre nodes in
+// symmetric pairs (m, m' = M-1-m), rho_m' = -rho_m, w_m' = w_m (the middle
+// node of an odd M runs alone).  With s_nu = S w_nu the field shifted by
+// node m (S = inv2(exp(i alpha_jm . b) fwd2(.)) / P^2) and the packed
+// convolutions Phi_a,b = Psi(w_a s_b), Psi = inv2(psi'_j / P^2 fwd2(.)):
+//   node m :  o_b  += c sum_a eta_a s_a Phi_a,b                 (real space)
+//   node m':  o'_a  = c S^{-1} sum_b eta_b w_b Phi_a,b
+// because translations commute with Psi and distribute over products whose
+// band stays inside the padded grid; the aliased part of the last product
+// falls outside Xi, which the output keeps.  o' is accumulated as a
+// spectrum, conj(phase) fwd2(sign_a o'_a) with the sign of the B term
+// (-1 for a = 0), packed (0 + i1), (2 + i3), into i3p[cell][j].
+// c = (pi/J) w_m.  Per pair: 2 shift transforms, 8 packed convolutions of 2
+// transforms each, 2 transforms of the partner sums.
+//
+// The nodes of a (cell, j) are cut into d.ng groups, one workgroup each, and
+// k_assemble adds the groups' sums.  The cut depends on M alone, so a cell's
+// result does not depend on how many cells share its launch.  At J = 32 one
+// cell is 128 workgroups of 4 node pairs (N = 32) instead of 32 of 16, which
+// left most of the chip idle; and a launch that does not fill its last round
+// of resident workgroups loses a quarter as much (40 cells at N = 32: 2.5
+// rounds of long tasks took the time of 3).  More groups would cost launches
+// that fill the chip more than the sums are worth: k_assemble reads the equal
+// of 5 planes per group (four groups: +1.5 % of a collision at N = 32).
+// Planes per task of the shifted-field buffer i3s: the four shifted
 // fields, and in float64 two more for partner sums that do not fit in
 // registers.
 template <typename T>
@@ -526,17 +548,19 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) __attribute__((amdgpu_waves_pe
   const unsigned tid = threadIdx.x;
   typename K::Eng eng;
   setup(eng, smem, d.tw);
-  // one (cell, j) task per workgroup, or grid-stride over the tasks when
-  // the launch is persistent (a grid that is a multiple of 8 keeps every
-  // cell's tasks on the XCD that runs them)
-  const int ntask = ncells * d.J;
+  // one (cell, j, group) task per workgroup, or grid-stride over the tasks
+  // when the launch is persistent (a grid that is a multiple of 8 keeps
+  // every cell's tasks on the XCD that runs them)
+  const int ntask = ncells * d.J * d.ng;
+  const int nnode = PAIR ? (d.M + 1) / 2 : d.M;
 #pragma unroll 1
   for (int pt = blockIdx.x; pt < ntask; pt += gridDim.x) {
   const int task = xcd_task(pt, ntask);
-  const int cell = task / d.J;
-  const int j = task % d.J;
+  const int cell = task / (d.J * d.ng);
+  const int j = task / d.ng % d.J;
+  const int mb = task % d.ng * d.gs, me = min(nnode, mb + d.gs);
   const unsigned vo = threadIdx.x * S;
-  const size_t tb = (size_t)cell * d.J + j;
+  const size_t tb = (size_t)task;
   const rsrc_t rs = mkbuf(d.spec + (size_t)cell * 8 * K::FSZ, 8 * K::FSZ);
   const rsrc_t rw = mkbuf(d.wP + (size_t)cell * 5 * K::FSZ, 5 * K::FSZ);
   const rsrc_t ro = mkbuf(d.i3o + tb * 4 * K::FSZ, 4 * K::FSZ);
@@ -544,10 +568,19 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) __attribute__((amdgpu_waves_pe
   const rsrc_t rb = mkbuf(SREG ? d.i3o : d.i3s + tb * kI3sPlanes<T> * K::FSZ, kI3sPlanes<T> * K::FSZ);
   const rsrc_t rm = mkbuf(d.psips + (size_t)j * K::FSZ, K::FSZ);
   const int kx = eng.line;
+  // the partner spectra matter on Xi only (k_combine keeps Xi): the other
+  // lanes' buffer accesses get an offset past the buffer, so their loads
+  // return 0 and their stores are dropped, without memory traffic and
+  // without a branch
+  const int bx = centered<P>(kx);
+  const bool kx_in = bx > -P / 4 && bx < P / 4;
+  auto xi_off = [&](int k) {
+    const int by = centered<P>(eng.bk(k));
+    return (kx_in && by > -P / 4 && by < P / 4) ? vo : 0x80000000u;
+  };
   T s[SREG ? 4 : 1][SREG ? E : 1];
-  const int nnode = PAIR ? (d.M + 1) / 2 : d.M;
 #pragma unroll 1
-  for (int m = 0; m < nnode; ++m) {
+  for (int m = mb; m < me; ++m) {
     const bool paired = PAIR && m != d.M - 1 - m;
     const T* px = d.phx + (((size_t)j * d.M + m) * P) * 2;
     const T* py = d.phy + (((size_t)j * d.M + m) * P) * 2 + 2 * E * eng.bq;
@@ -562,11 +595,10 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) __attribute__((amdgpu_waves_pe
         const unsigned o = k * K::NT;
         T er, ei;
         cmul(pxr, pxi, py[2 * k], py[2 * k + 1], er, ei);
-        T ar, ai, br, bi;
-        cmul(bld<T>(rs, vo, (fa + o) * S), bld<T>(rs, vo, (fa + K::FSZ + o) * S), er, ei, ar, ai);
-        cmul(bld<T>(rs, vo, (fb + o) * S), bld<T>(rs, vo, (fb + K::FSZ + o) * S), er, ei, br, bi);
-        zr[k] = ar - bi;
-        zi[k] = ai + br;
+        // (a + i b) e
+        const T xr = bld<T>(rs, vo, (fa + o) * S) - bld<T>(rs, vo, (fb + K::FSZ + o) * S);
+        const T xi = bld<T>(rs, vo, (fa + K::FSZ + o) * S) + bld<T>(rs, vo, (fb + o) * S);
+        cmul(xr, xi, er, ei, zr[k], zi[k]);
         if (k % SG == SG - 1) __builtin_amdgcn_sched_barrier(0);
       }
       eng.inv2(zr, zi);
@@ -602,7 +634,7 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) __attribute__((amdgpu_waves_pe
           rbv[AREG ? n : 0] = bld<T>(rb, vo, (m1 * K::FSZ + n * K::NT) * S);
         }
       }
-      const bool first = m == 0 && mp == 0;
+      const bool first = m == mb && mp == 0;
 #pragma unroll 1
       for (int nu = 0; nu < 4; ++nu) {
         // (fetched on the first pass too, where the values go unused: a
@@ -680,18 +712,8 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) __attribute__((amdgpu_waves_pe
           if (n % SG == SG - 1) __builtin_amdgcn_sched_barrier(0);
         }
       }
-      // spectrum of the partner sums: conj(phase) fwd2(pa + i pb), accumulated.
-      // Only its entries on Xi reach the output (k_combine keeps Xi), so
-      // the other lanes' buffer accesses get an offset past the buffer:
-      // their loads return 0 and their stores are dropped, without memory
-      // traffic and without a branch.
+      // spectrum of the partner sums: conj(phase) fwd2(pa + i pb), accumulated on Xi
       const unsigned fr = (2 * mp) * K::FSZ, fi = (2 * mp + 1) * K::FSZ;
-      const int bx = centered<P>(kx);
-      const bool kx_in = bx > -P / 4 && bx < P / 4;
-      auto xi_off = [&](int k) {
-        const int by = centered<P>(eng.bk(k));
-        return (kx_in && by > -P / 4 && by < P / 4) ? vo : 0x80000000u;
-      };
       if (paired) {
         T zr[E], zi[E];
 #pragma unroll
@@ -715,13 +737,13 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) __attribute__((amdgpu_waves_pe
           cmul(zr[k], zi[k], er, -ei, xr, xi);
           const T pr0 = bld<T>(rp, vk, (fr + o) * S);
           const T pi0 = bld<T>(rp, vk, (fi + o) * S);
-          xr += m != 0 ? pr0 : (T)0;
-          xi += m != 0 ? pi0 : (T)0;
+          xr += m != mb ? pr0 : (T)0;
+          xi += m != mb ? pi0 : (T)0;
           bst<T>(rp, xr, vk, (fr + o) * S);
           bst<T>(rp, xi, vk, (fi + o) * S);
           if (k % SG == SG - 1) __builtin_amdgcn_sched_barrier(0);
         }
-      } else if (m == 0) {
+      } else if (m == mb) {
         // no partner spectrum (unpaired kernel, or a single node)
 #pragma unroll
         for (int k = 0; k < E; ++k) {
@@ -743,55 +765,119 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) __attribute__((amdgpu_waves_pe
   }  // tasks
 }
 
-// Real-space P-grid fields of C, elementwise: sums the per-j partials of I_3
-// and assembles the Pauli components (C_c + pi (A + B + Cq), see k_combine)
-// into i3sum[cell][mu]; sums the partner-node spectra of I_3 into i3ps on
-// Xi (the only entries k_i3 writes and k_combine reads; 0 elsewhere).
+// Real-space P-grid fields of C, elementwise: sums the per-task partials of
+// I_3 (group by group, then over j) and of k_terms, and assembles the Pauli
+// components (C_c + pi (A + B + Cq), see k_combine) into i3sum[cell][mu];
+// sums the partner-node spectra of I_3 into i3ps on Xi (the only entries k_i3
+// writes and k_combine reads; 0 elsewhere).
+// Bound by reading the partials.  Each of a workgroup's 8 rows of 32 threads
+// takes every 8th j, 16 bytes per thread and load; the rows' sums are added
+// in the order of the rows.  (One thread per element over all j, 4 or 8 bytes
+// a load, left one cell with 4096 threads and read at 3.7 TB/s.)
+constexpr int kAsmRow = 8;
+template <typename T>
+constexpr int kAsmEl = 32 * 16 / (int)sizeof(T);
 template <typename T, int P, int E>
-__global__ void k_assemble(DevPlan<T> d, int ncells) {
+__global__ __launch_bounds__(32 * kAsmRow) void k_assemble(DevPlan<T> d, int ncells) {
   using Eng = Fft2<T, P, E>;
-  constexpr int fsz = P * P;
-  const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (size_t)ncells * fsz) return;
-  const size_t cell = idx / fsz, e = idx % fsz;
+  constexpr int fsz = P * P, V = 16 / (int)sizeof(T), EL = kAsmEl<T>;
+  typedef T vec __attribute__((ext_vector_type(V)));
+  static_assert(fsz % EL == 0, "a workgroup stays in one cell");
+  __shared__ vec red[kAsmRow][8][32];
+  __shared__ vec tr[kTermPlanes][32];
+  const int el = threadIdx.x % 32, row = threadIdx.x / 32;
+  const int cell = blockIdx.x / (fsz / EL);
+  const int e = (blockIdx.x % (fsz / EL)) * EL + V * el;
   const size_t per = (size_t)4 * fsz;
-  // col spec position e = k NT + t: frequency (kx, ky) = (t / TPR, k + E bitrev(q))
-  const int t = (int)(e % Eng::NT), kk = (int)(e / Eng::NT);
-  const int bx = centered<P>(t / Eng::TPR);
-  const int by = centered<P>(kk + E * bitrev_rt(Eng::lane_label(t % Eng::TPR), Eng::LB));
-  const bool on_xi = bx > -P / 4 && bx < P / 4 && by > -P / 4 && by < P / 4;
-  const T* o3 = d.i3o + cell * d.J * per + e;
-  const T* p3 = d.i3p + cell * d.J * per + e;
-  T b[4] = {0, 0, 0, 0}, q[4] = {0, 0, 0, 0};
-  for (int j = 0; j < d.J; ++j)
+  auto ld = [](const T* p) { return *(const vec*)p; };
+  vec on;  // 1 on Xi
+  bool any = false;
+#pragma unroll
+  for (int v = 0; v < V; ++v) {
+    // col spec position e = k NT + t: frequency (kx, ky) = (t / TPR, k + E bitrev(q))
+    const int t = (e + v) % Eng::NT, kk = (e + v) / Eng::NT;
+    const int bx = centered<P>(t / Eng::TPR);
+    const int by = centered<P>(kk + E * bitrev_rt(Eng::lane_label(t % Eng::TPR), Eng::LB));
+    const bool on_xi = bx > -P / 4 && bx < P / 4 && by > -P / 4 && by < P / 4;
+    on[v] = on_xi ? (T)1 : (T)0;
+    any |= on_xi;
+  }
+  vec b[4], q[4];
+#pragma unroll
+  for (int nu = 0; nu < 4; ++nu) b[nu] = q[nu] = (vec)(T)0;
+  const size_t base = (size_t)cell * d.J * d.ng;
+  for (int j = row; j < d.J; j += kAsmRow) {
+    const T* o3 = d.i3o + (base + (size_t)j * d.ng) * per + e;
+    const T* p3 = d.i3p + (base + (size_t)j * d.ng) * per + e;
+    vec bj[4], qj[4];
+#pragma unroll
     for (int nu = 0; nu < 4; ++nu) {
-      b[nu] += o3[(size_t)j * per + (size_t)nu * fsz];
-      if (on_xi) q[nu] += p3[(size_t)j * per + (size_t)nu * fsz];
+      bj[nu] = ld(o3 + (size_t)nu * fsz);
+      if (any) qj[nu] = ld(p3 + (size_t)nu * fsz);
     }
-  T* ps = d.i3ps + cell * per + e;
-  for (int nu = 0; nu < 4; ++nu) ps[(size_t)nu * fsz] = q[nu];
-  const T* wp = d.wP + cell * 5 * fsz + e;
-  const T* tr = d.terms + cell * kTermPlanes * fsz + e;
-  const T w0 = wp[0], w1 = wp[fsz], w2 = wp[2 * fsz], w3 = wp[3 * fsz];
-  const T g1 = tr[0], g2 = tr[fsz], g3 = tr[2 * fsz];
-  const T y0 = tr[3 * fsz], y1 = tr[4 * fsz], y2 = tr[5 * fsz], y3 = tr[6 * fsz];
-  const T Sv = (tr[7 * fsz] + tr[8 * fsz]) + (tr[9 * fsz] + tr[10 * fsz]);
+    for (int g = 1; g < d.ng; ++g) {
+      o3 += per;
+      p3 += per;
+#pragma unroll
+      for (int nu = 0; nu < 4; ++nu) {
+        bj[nu] += ld(o3 + (size_t)nu * fsz);
+        if (any) qj[nu] += ld(p3 + (size_t)nu * fsz);
+      }
+    }
+#pragma unroll
+    for (int nu = 0; nu < 4; ++nu) {
+      b[nu] += bj[nu];
+      if (any) q[nu] += qj[nu];
+    }
+  }
+#pragma unroll
+  for (int nu = 0; nu < 4; ++nu) {
+    red[row][nu][el] = b[nu];
+    red[row][4 + nu][el] = q[nu];
+  }
+  for (int f = row; f < kTermPlanes; f += kAsmRow) {
+    const T* tp = d.terms + ((size_t)cell * kTermPlanes + f) * d.tg * fsz + e;
+    vec a = ld(tp);
+    for (int g = 1; g < d.tg; ++g) a += ld(tp + (size_t)g * fsz);
+    tr[f][el] = a;
+  }
+  __syncthreads();
+  // rows 0..3 finish component mu = row of C, rows 4..7 the partner spectra
+  vec sum = red[0][row][el];
+  for (int r = 1; r < kAsmRow; ++r) sum += red[r][row][el];
+  if (row >= 4) {
+    // entries off Xi were never written: dropped by a select
+#pragma unroll
+    for (int v = 0; v < V; ++v) sum[v] = on[v] != (T)0 ? sum[v] : (T)0;
+    *(vec*)(d.i3ps + (size_t)cell * per + (size_t)(row - 4) * fsz + e) = sum;
+    return;
+  }
+  const T* wp = d.wP + (size_t)cell * 5 * fsz + e;
+  const vec w0 = ld(wp);
+  const vec y0 = tr[3][el], Sv = (tr[7][el] + tr[8][el]) + (tr[9][el] + tr[10][el]);
   const T pi = (T)kPi, two = (T)2;
-  T* r = d.i3sum + cell * per + e;
   // A: 2 <w3, w4>_eta (1 - W1); B: -2 <w3, w4>_eta (eta w2).sigma;
   // Cq: f0(v+u) {W1, (eta w2).sigma};  C_c,k = -2 eps_klm A^G_l w_m
   const T pd = d.wd * pi, wc = d.wc;
-  r[0] = pd * (two * Sv * ((T)1 - w0) - two * b[0] + two * (y0 * w0 - y1 * w1 - y2 * w2 - y3 * w3));
-  r[fsz] = -wc * two * (g2 * w3 - g3 * w2) + pd * (-two * Sv * w1 + two * b[1] + two * (y0 * w1 - y1 * w0));
-  r[2 * fsz] = -wc * two * (g3 * w1 - g1 * w3) + pd * (-two * Sv * w2 + two * b[2] + two * (y0 * w2 - y2 * w0));
-  r[3 * fsz] = -wc * two * (g1 * w2 - g2 * w1) + pd * (-two * Sv * w3 + two * b[3] + two * (y0 * w3 - y3 * w0));
+  vec r;
+  if (row == 0) {
+    const vec w1 = ld(wp + fsz), w2 = ld(wp + 2 * fsz), w3 = ld(wp + 3 * fsz);
+    r = pd * (two * Sv * ((T)1 - w0) - two * sum + two * (y0 * w0 - tr[4][el] * w1 - tr[5][el] * w2 - tr[6][el] * w3));
+  } else {
+    const int l = row % 3 + 1, m = (row + 1) % 3 + 1;  // (row, l, m) cyclic
+    const vec wk = ld(wp + row * fsz), wl = ld(wp + l * fsz), wm = ld(wp + m * fsz);
+    r = -wc * two * (tr[l - 1][el] * wm - tr[m - 1][el] * wl) +
+        pd * (-two * Sv * wk + two * sum + two * (y0 * wk - tr[3 + row][el] * w0));
+  }
+  *(vec*)(d.i3sum + (size_t)cell * per + (size_t)row * fsz + e) = r;
 }
 
 // ------------------------------------------------------------------ combine
 // Transform the assembled real-space P-grid fields of C (Pauli components,
 // k_assemble), add the partner-node spectra of I_3 (times 2 pi, the B term
 // with its sign already applied), keep Xi without its -N/2 rows and
-// columns, and evaluate on the velocity grid:  c[mu][cell][i][j].
+// columns, and evaluate on the velocity grid:  c[mu][cell][i][j].  One
+// workgroup per (cell, pair of components).
 template <typename T, int P, int E>
 __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_combine(DevPlan<T> d, T* __restrict__ c, int cell0) {
   using K = Kern<T, P, E>;
@@ -799,15 +885,14 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_combine(DevPlan<T> d, T
   __shared__ T smem[K::LDS];
   Fft2<T, P, E> eng;
   setup(eng, smem, d.tw);
-  const int lc = blockIdx.x;
+  const int lc = blockIdx.x >> 1, pr = blockIdx.x & 1;
   const int cell = cell0 + lc;
   const int N = P / 2;
   const unsigned vo = threadIdx.x * S;
   const rsrc_t r3 = mkbuf(d.i3sum + (size_t)lc * 4 * K::FSZ, 4 * K::FSZ);
   const rsrc_t rps = mkbuf(d.i3ps + (size_t)lc * 4 * K::FSZ, 4 * K::FSZ);
   const size_t cs = (size_t)d.Nx * N * N;
-#pragma unroll 1
-  for (int pr = 0; pr < 2; ++pr) {
+  {
     T zr[E], zi[E];
 #pragma unroll
     for (int n = 0; n < E; ++n) {

@@ -395,13 +395,20 @@ struct CollBufs {
        *i3sum = nullptr, *i3p = nullptr, *i3ps = nullptr;
 };
 
+// The buffers of C cells, I_3 in launches of I cells; with `one` (a single
+// summation group everywhere) the least that the pipeline runs in.
 template <typename T>
-bool carve_collision(Arena& a, const qb_plan_s* pl, size_t C, CollBufs& b) {
+bool carve_collision(Arena& a, const qb_plan_s* pl, size_t C, size_t I, bool one, CollBufs& b) {
   const size_t FSZ = (size_t)pl->P * pl->P, J = pl->prob.J, t = sizeof(T);
-  return a.take(&b.i3s, C * J * qb::kI3sPlanes<T> * FSZ * t) && a.take(&b.spec, C * 8 * FSZ * t) &&
-         a.take(&b.wP, C * 5 * FSZ * t) && a.take(&b.terms, C * qb::kTermPlanes * FSZ * t) && a.take(&b.acc, C * 14 * FSZ * t) &&
-         a.take(&b.i3o, C * J * 4 * FSZ * t) && a.take(&b.i3sum, C * 4 * FSZ * t) &&
-         a.take(&b.i3p, C * J * 4 * FSZ * t) && a.take(&b.i3ps, C * 4 * FSZ * t);
+  const size_t ng = one ? 1 : max_node_groups(pl->prob), tg = term_groups(pl->prob.J, one);
+  // the spectral accumulators of k_terms are in memory for some float64 tiles
+  // only; k_terms_vjp keeps one set per cell there
+  const size_t ta = sizeof(T) == 8 && pl->P >= 64 ? tg : 1;
+  const size_t tasks = I * J * ng;
+  return a.take(&b.i3s, tasks * qb::kI3sPlanes<T> * FSZ * t) && a.take(&b.spec, C * 8 * FSZ * t) &&
+         a.take(&b.wP, C * 5 * FSZ * t) && a.take(&b.terms, C * qb::kTermPlanes * tg * FSZ * t) &&
+         a.take(&b.acc, C * 14 * ta * FSZ * t) && a.take(&b.i3o, tasks * 4 * FSZ * t) &&
+         a.take(&b.i3sum, C * 4 * FSZ * t) && a.take(&b.i3p, tasks * 4 * FSZ * t) && a.take(&b.i3ps, C * 4 * FSZ * t);
 }
 
 CollBufs get_bufs(const qb_plan_s* pl) {
@@ -421,7 +428,7 @@ bool build_buffers(qb_plan_s* pl) {
   const qb_problem& p = pl->prob;
   const size_t st = (size_t)4 * p.Nx * p.N * p.N * sizeof(T);
   CollBufs b;
-  if (!carve_collision<T>(pl->ws, pl, pl->wcells, b)) {
+  if (!carve_collision<T>(pl->ws, pl, pl->wcells, pl->i3cells, false, b)) {
     set_error("plan workspace exhausted");
     return false;
   }
@@ -1033,6 +1040,7 @@ void init_plan(qb_plan_s* pl, const qb_problem& problem, int max_cells) {
   pl->TPR = pl->P / pl->E;
   pl->NT = pl->P * pl->TPR;
   pl->wcells = chunk_cells(problem, max_cells);
+  pl->i3cells = i3_launch_cells(problem, pl->wcells);
 }
 
 // Carve (and, unless measuring, fill) everything a plan holds: phases and
@@ -1300,7 +1308,7 @@ size_t static_bytes(const qb_plan_s* pl, int n) {
   CollBufs b;
   void* x = nullptr;
   const size_t st = (size_t)4 * n * pl->prob.N * pl->prob.N * sizeof(T);
-  carve_collision<T>(a, pl, n, b);
+  carve_collision<T>(a, pl, n, n, true, b);
   a.take(&x, st);
   a.take(&x, st);
   return a.used;
@@ -1336,19 +1344,20 @@ qb_status do_collision_static(qb_plan_s* pl, void* base, const void* W, void* C,
   void *w = nullptr, *c = nullptr;
   const size_t per = (size_t)pl->prob.N * pl->prob.N;
   const size_t st = 4 * (size_t)chunk * per * sizeof(T);
-  if (!carve_collision<T>(a, pl, chunk, b) || !a.take(&w, st) || !a.take(&c, st)) {
+  if (!carve_collision<T>(a, pl, chunk, chunk, true, b) || !a.take(&w, st) || !a.take(&c, st)) {
     set_error("static scratch exhausted");
     return QB_EWORKSPACE;
   }
   const CollBufs keep = get_bufs(pl);
-  const int keep_nx = pl->prob.Nx, keep_wc = pl->wcells;
+  const int keep_nx = pl->prob.Nx, keep_wc = pl->wcells, keep_ic = pl->i3cells;
   set_bufs(pl, b);
+  pl->one_group = true;  // as many cells as fit
   bool ok = true;
   for (int c0 = 0; c0 < ncells && ok; c0 += chunk) {
     const int n = std::min(chunk, ncells - c0);
     // state arrays of the chunk hold n cells per Pauli component
     pl->prob.Nx = n;
-    pl->wcells = n;
+    pl->wcells = pl->i3cells = n;
     const T* Wc = (const T*)W + (size_t)c0 * per * 8;
     T* Cc = (T*)C + (size_t)c0 * per * 8;
     hipLaunchKernelGGL((qb::k_api_to_state<T, T>), dim3(blocks(n * per, 256)), dim3(256), 0, s, Wc, (T*)w, n,
@@ -1361,8 +1370,10 @@ qb_status do_collision_static(qb_plan_s* pl, void* base, const void* W, void* C,
     }
   }
   set_bufs(pl, keep);
+  pl->one_group = false;
   pl->prob.Nx = keep_nx;
   pl->wcells = keep_wc;
+  pl->i3cells = keep_ic;
   return ok ? QB_OK : QB_EHIP;
 }
 

@@ -10,7 +10,7 @@ bool collision_pipeline(qb_plan_s* pl, const T* w, T* c, int ncells, int cell0, 
   constexpr int NT = qb::Fft2<T, P, E>::NT;
   DevPlan<T> d = devplan<T>(pl, pl->cur_tab);
   int id = pl->begin(QB_K_DFT_IN, s);
-  hipLaunchKernelGGL((qb::k_dft_in<T, P, E>), dim3(ncells), dim3(NT), 0, s, d, w, cell0);
+  hipLaunchKernelGGL((qb::k_dft_in<T, P, E>), dim3(4 * ncells), dim3(NT), 0, s, d, w, cell0);
   pl->end(id, s);
   // persistent launches: at most the workgroups that are resident at once
   // (rounded down to a multiple of 8), grid-striding over the task list
@@ -18,21 +18,33 @@ bool collision_pipeline(qb_plan_s* pl, const T* w, T* c, int ncells, int cell0, 
     return pl->persistent ? std::min(ntask, persistent_grid(kern, NT)) : ntask;
   };
   id = pl->begin(QB_K_TERMS, s);
-  hipLaunchKernelGGL((qb::k_terms<T, P, E>), dim3(grid(ncells * qb::kTermPlanes, (const void*)qb::k_terms<T, P, E>)), dim3(NT),
-                     0, s, d, ncells);
+  hipLaunchKernelGGL((qb::k_terms<T, P, E>),
+                     dim3(grid(ncells * qb::kTermPlanes * d.tg, (const void*)qb::k_terms<T, P, E>)), dim3(NT), 0, s, d,
+                     ncells);
   pl->end(id, s);
+  // I_3 and its sums in launches of at most i3cells cells (their buffers)
   id = pl->begin(QB_K_I3, s);
-  if (pl->i3_pair)
-    hipLaunchKernelGGL((qb::k_i3<T, P, E, true>), dim3(grid(ncells * d.J, (const void*)qb::k_i3<T, P, E, true>)),
-                       dim3(NT), 0, s, d, ncells);
-  else
-    hipLaunchKernelGGL((qb::k_i3<T, P, E, false>), dim3(grid(ncells * d.J, (const void*)qb::k_i3<T, P, E, false>)),
-                       dim3(NT), 0, s, d, ncells);
+  for (int c0 = 0; c0 < ncells; c0 += pl->i3cells) {
+    const int nc = std::min(pl->i3cells, ncells - c0);
+    DevPlan<T> dc = d;
+    dc.spec += (size_t)c0 * 8 * P * P;
+    dc.wP += (size_t)c0 * 5 * P * P;
+    dc.terms += (size_t)c0 * qb::kTermPlanes * d.tg * P * P;
+    dc.i3sum += (size_t)c0 * 4 * P * P;
+    dc.i3ps += (size_t)c0 * 4 * P * P;
+    const int ntask = nc * d.J * d.ng;
+    if (pl->i3_pair)
+      hipLaunchKernelGGL((qb::k_i3<T, P, E, true>), dim3(grid(ntask, (const void*)qb::k_i3<T, P, E, true>)), dim3(NT),
+                         0, s, dc, nc);
+    else
+      hipLaunchKernelGGL((qb::k_i3<T, P, E, false>), dim3(grid(ntask, (const void*)qb::k_i3<T, P, E, false>)),
+                         dim3(NT), 0, s, dc, nc);
+    hipLaunchKernelGGL((qb::k_assemble<T, P, E>), dim3(nc * (P * P / qb::kAsmEl<T>)), dim3(32 * qb::kAsmRow), 0, s, dc,
+                       nc);
+  }
   pl->end(id, s);
-  const size_t nel = (size_t)ncells * P * P;
-  hipLaunchKernelGGL((qb::k_assemble<T, P, E>), dim3(blocks(nel, 256)), dim3(256), 0, s, d, ncells);
   id = pl->begin(QB_K_COMBINE, s);
-  hipLaunchKernelGGL((qb::k_combine<T, P, E>), dim3(ncells), dim3(NT), 0, s, d, c, cell0);
+  hipLaunchKernelGGL((qb::k_combine<T, P, E>), dim3(2 * ncells), dim3(NT), 0, s, d, c, cell0);
   pl->end(id, s);
   return hip_ok(hipGetLastError(), "collision launch");
 }
@@ -44,7 +56,7 @@ bool collision_vjp_pipeline(qb_plan_s* pl, const T* w, const T* lam, T* out, int
   constexpr int NT = qb::Fft2<T, P, E>::NT;
   DevPlan<T> d = devplan<T>(pl, pl->vjp_tab);
   int id = pl->begin(QB_K_DFT_IN, s);
-  hipLaunchKernelGGL((qb::k_dft_in<T, P, E>), dim3(ncells), dim3(NT), 0, s, d, w, cell0);
+  hipLaunchKernelGGL((qb::k_dft_in<T, P, E>), dim3(4 * ncells), dim3(NT), 0, s, d, w, cell0);
   pl->end(id, s);
   // the forward I_1 / I_4 / I_2 fields are formed inside k_terms_vjp
   id = pl->begin(QB_K_ADJOINT, s);

@@ -4,6 +4,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <string>
 #include <vector>
 
@@ -54,6 +55,8 @@ struct qb_plan_s {
   Arena adj;  // the reverse-mode workspace (qb_plan_enable_adjoint)
   int P, E, NT, TPR;
   int wcells;  // cells per collision launch (the workspace holds this many)
+  int i3cells;  // cells per launch of k_i3 (its buffers hold this many)
+  bool one_group = false;  // one summation group each in k_i3 and k_terms (the least workspace)
   bool i3_pair = true;  // I_3 kernel pairs the Gauss-Legendre nodes (tuned; default per tile)
   int vjp_variant = 0;  // I_3 adjoint: 0 row w_bar in memory, 1 in registers (tuned)
   int vjp_E = 0;        // tile shape of the reverse-mode pipeline (tuned; 0: the forward tile)
@@ -137,6 +140,31 @@ struct qb_plan_s {
   }
 };
 
+// Summation groups of the I_3 nodes (pairs of nodes when paired; see k_i3):
+// 4 nodes to a group, 2 or 3 where there are too few for 4 groups.
+inline void node_groups(int nnode, bool one, int& gs, int& ng) {
+  gs = one ? nnode : std::min(4, std::max(2, (nnode + 3) / 4));
+  ng = (nnode + gs - 1) / gs;
+}
+inline int max_node_groups(const qb_problem& p) {
+  int gs, a, b;
+  node_groups((p.M + 1) / 2, false, gs, a);
+  node_groups(p.M, false, gs, b);
+  return std::max(a, b);
+}
+// Directions per group of k_terms: 4 pairs, 8 transforms beside the final one.
+constexpr int kTermDirs = 8;
+inline int term_groups(int J, bool one) { return one ? 1 : (J + kTermDirs - 1) / kTermDirs; }
+
+// Cells per launch of k_i3 in chunks of wcells cells: enough tasks for the
+// partly empty last round of a launch not to matter (some 30 rounds of the
+// resident workgroups), and no more I_3 buffers than `wcells` cells with one
+// task per (cell, j) would take beyond that.
+inline int i3_launch_cells(const qb_problem& p, int wcells) {
+  const int ng = max_node_groups(p);
+  const int tasks = p.N == 16 ? 65536 : p.N == 32 ? 32768 : 16384;
+  return std::min(wcells, std::max((wcells + ng - 1) / ng, tasks / (p.J * ng)));
+}
 
 // Device view of the plan with the table set `tab` (the forward pipeline
 // uses cur_tab, the reverse-mode pipeline vjp_tab).
@@ -172,6 +200,9 @@ inline DevPlan<T> devplan(qb_plan_s* pl, int tab) {
   d.i3sum = (T*)pl->i3sum;
   d.i3p = (T*)pl->i3p;
   d.i3ps = (T*)pl->i3ps;
+  node_groups(pl->i3_pair ? (d.M + 1) / 2 : d.M, pl->one_group, d.gs, d.ng);
+  d.tg = term_groups(d.J, pl->one_group);
+  d.td = pl->one_group ? d.J : kTermDirs;
   d.lamP = (T*)pl->lamP;
   d.acot = (T*)pl->acot;
   d.gspec = (T*)pl->gspec;
