@@ -69,7 +69,7 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_lam_in(DevPlan<T> d, co
   using K = Kern<T, P, E>;
   constexpr unsigned S = sizeof(T);
   __shared__ T smem[K::LDS];
-  Fft2<T, P, E> eng;
+  typename K::Eng eng;
   setup(eng, smem, d.tw);
   const int lc = blockIdx.x;
   const int cell = cell0 + lc;
@@ -94,7 +94,7 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_lam_in(DevPlan<T> d, co
       zr[n] = on_grid ? la[i * N] : (T)0;
       zi[n] = on_grid ? lb[i * N] : (T)0;
     }
-    eng.fwd2(zr, zi);
+    eng.template fwd2<true>(zr, zi);
 #pragma unroll
     for (int k = 0; k < E; ++k) {
       const int by = centered<P>(eng.bk(k));
@@ -105,7 +105,7 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_lam_in(DevPlan<T> d, co
       bst<T>(rh, zr[k], vo, ((2 * pr) * K::FSZ + k * K::NT) * S);
       bst<T>(rh, zi[k], vo, ((2 * pr + 1) * K::FSZ + k * K::NT) * S);
     }
-    eng.inv2(zr, zi);
+    eng.template inv2<true>(zr, zi);
 #pragma unroll
     for (int n = 0; n < E; ++n) {
       bst<T>(ro, zr[n], vo, ((2 * pr) * K::FSZ + n * K::NT) * S);
@@ -198,7 +198,7 @@ __attribute__((amdgpu_waves_per_eu(Fft2<T, P, E>::NT >= 512 ? 4 : 1))) void k_te
   using K = Kern<T, P, E>;
   constexpr unsigned S = sizeof(T);
   __shared__ T smem[K::LDS];
-  Fft2<T, P, E> eng;
+  typename K::Eng eng;
   setup(eng, smem, d.tw);
   const int cell = blockIdx.x / kTermsVjpTasks;
   const int task = blockIdx.x % kTermsVjpTasks;
@@ -227,7 +227,7 @@ __attribute__((amdgpu_waves_per_eu(Fft2<T, P, E>::NT >= 512 ? 4 : 1))) void k_te
         zr[n] = bld<T>(ra, vo, (task * K::FSZ + n * K::NT) * S);
         zi[n] = 0;
       }
-      eng.fwd2(zr, zi);
+      eng.template fwd2<true>(zr, zi);
 #pragma unroll
       for (int k = 0; k < E; ++k) {
         bst<T>(rd, zr[k], vo, (k * K::NT) * S);
@@ -250,7 +250,7 @@ __attribute__((amdgpu_waves_per_eu(Fft2<T, P, E>::NT >= 512 ? 4 : 1))) void k_te
         zr[k] = cr * dr - ci * di;
         zi[k] = cr * di + ci * dr;
       }
-      eng.inv2(zr, zi);
+      eng.template inv2<true>(zr, zi);
 #pragma unroll
       for (int n = 0; n < E; ++n) {
         Br[n] = zr[n];
@@ -280,7 +280,7 @@ __attribute__((amdgpu_waves_per_eu(Fft2<T, P, E>::NT >= 512 ? 4 : 1))) void k_te
         zi[n] *= f0;
       }
       // the pair's forward contribution cout fwd2(f0 A)
-      eng.fwd2(zr, zi);
+      eng.template fwd2<true>(zr, zi);
 #pragma unroll
       for (int k = 0; k < E; ++k) {
         const unsigned o = k * K::NT;
@@ -325,7 +325,7 @@ __attribute__((amdgpu_waves_per_eu(Fft2<T, P, E>::NT >= 512 ? 4 : 1))) void k_te
       zr[k] = bld<T>(rc, vo, o * S);
       zi[k] = bld<T>(rc, vo, (K::FSZ + o) * S);
     }
-    eng.inv2(zr, zi);
+    eng.template inv2<true>(zr, zi);
 #pragma unroll
     for (int n = 0; n < E; ++n) bst<T>(ro, zr[n], vo, (n * K::NT) * S);
   } else {
@@ -352,7 +352,7 @@ __attribute__((amdgpu_waves_per_eu(Fft2<T, P, E>::NT >= 512 ? 4 : 1))) void k_te
         zr[k] = ar * a - ai * b;
         zi[k] = ai * a + ar * b;
       }
-      eng.inv2(zr, zi);  // (A, B)
+      eng.template inv2<true>(zr, zi);  // (A, B)
 #pragma unroll
       for (int n = 0; n < E; ++n) {
         Sacc[n] += e * zr[n] * zi[n];  // the forward accumulator's share
@@ -361,7 +361,7 @@ __attribute__((amdgpu_waves_per_eu(Fft2<T, P, E>::NT >= 512 ? 4 : 1))) void k_te
         zr[n] = sb * zi[n];  // S_bar e B
         zi[n] = sb * A;      // S_bar e A
       }
-      eng.fwd2(zr, zi);
+      eng.template fwd2<true>(zr, zi);
 #pragma unroll
       for (int k = 0; k < E; ++k) {
         const unsigned o = k * K::NT;
@@ -414,7 +414,7 @@ __attribute__((amdgpu_waves_per_eu(Fft2<T, P, E>::NT >= 512 ? 4 : 1))) void k_te
 // (mu 0 + i mu 1), (mu 2 + i mu 3), re/im planes, col spec.
 template <typename T, int P, int E, bool WREG>
 __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_i3_vjp_reg(DevPlan<T> d, int ncells) {
-  using K = Kern<T, P, E, true>;
+  using K = Kern<T, P, E, I3Regs<T, P, E>::XB>;
   constexpr unsigned S = sizeof(T);
   // elements between scheduling barriers in the element loops, which bound
   // the loads in flight
@@ -466,14 +466,14 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_i3_vjp_reg(DevPlan<T> d
       for (int n = 0; n < E; ++n) bst<T>(rg, (T)0, vo, (q * K::FSZ + n * K::NT) * S);
   }
   auto conv = [&](T (&zr)[E], T (&zi)[E]) {
-    eng.fwd2(zr, zi);
+    eng.template fwd2<true>(zr, zi);
 #pragma unroll
     for (int k = 0; k < E; ++k) {
       const T a = bld<T>(rm, vo, (k * K::NT) * S);
       zr[k] *= a;
       zi[k] *= a;
     }
-    eng.inv2(zr, zi);
+    eng.template inv2<true>(zr, zi);
   };
   auto ld = [&](rsrc_t r, int plane, unsigned o) { return bld<T>(r, vo, (plane * K::FSZ + o) * S); };
   auto rmw = [&](rsrc_t r, int plane, unsigned o, T v) {
@@ -709,16 +709,18 @@ __global__ void k_grad_pre(DevPlan<T> d, int ncells, int fsz) {
     // task slots of gspec: I_1 (mu >= 1) at mu - 1, I_4 at 3 + mu, I_2 at 7 + mu
     // k_terms_vjp leaves H with the cotangent (H(k) + conj H(-k)) / 2
     const T* gs = d.gspec + cell * 22 * fsz + e;
-    const T* gn = d.gspec + cell * 22 * fsz + d.negk[e];
+    const unsigned ne = d.negk[e];
+    const T* gn = d.gspec + cell * 22 * fsz + (ne & 0x7fffffffu);
+    const T sn = (ne >> 31) ? (T)-1 : (T)1;  // the kept spectra's signs at -k and k differ
     T ar = 0, ai = 0, br = 0, bi = 0;
     const int sa[3] = {ma - 1, 3 + ma, 7 + ma}, sb[3] = {mb - 1, 3 + mb, 7 + mb};
     for (int t = 0; t < 3; ++t) {
       if (sa[t] >= 0) {
-        ar += gs[(size_t)(2 * sa[t]) * fsz] + gn[(size_t)(2 * sa[t]) * fsz];
-        ai += gs[(size_t)(2 * sa[t] + 1) * fsz] - gn[(size_t)(2 * sa[t] + 1) * fsz];
+        ar += gs[(size_t)(2 * sa[t]) * fsz] + sn * gn[(size_t)(2 * sa[t]) * fsz];
+        ai += gs[(size_t)(2 * sa[t] + 1) * fsz] - sn * gn[(size_t)(2 * sa[t] + 1) * fsz];
       }
-      br += gs[(size_t)(2 * sb[t]) * fsz] + gn[(size_t)(2 * sb[t]) * fsz];
-      bi += gs[(size_t)(2 * sb[t] + 1) * fsz] - gn[(size_t)(2 * sb[t] + 1) * fsz];
+      br += gs[(size_t)(2 * sb[t]) * fsz] + sn * gn[(size_t)(2 * sb[t]) * fsz];
+      bi += gs[(size_t)(2 * sb[t] + 1) * fsz] - sn * gn[(size_t)(2 * sb[t] + 1) * fsz];
     }
     a += (T)0.5 * (im == 0 ? ar - bi : ai + br);
   }
@@ -735,7 +737,7 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_grad_out(DevPlan<T> d, 
   using K = Kern<T, P, E>;
   constexpr unsigned S = sizeof(T);
   __shared__ T smem[K::LDS];
-  Fft2<T, P, E> eng;
+  typename K::Eng eng;
   setup(eng, smem, d.tw);
   const int lc = blockIdx.x;
   const int cell = cell0 + lc;
@@ -756,7 +758,7 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_grad_out(DevPlan<T> d, 
       zr[n] = bld<T>(r3, vo, (ma * K::FSZ + o) * S);
       zi[n] = -bld<T>(r3, vo, (mb * K::FSZ + o) * S);
     }
-    eng.fwd2(zr, zi);  // conj(F)(a + i b) = conj(fwd2(a - i b))
+    eng.template fwd2<true>(zr, zi);  // conj(F)(a + i b) = conj(fwd2(a - i b))
 #pragma unroll
     for (int k = 0; k < E; ++k) {
       const unsigned o = k * K::NT;
@@ -768,7 +770,7 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_grad_out(DevPlan<T> d, 
       zr[k] = in ? Zr * sc : (T)0;
       zi[k] = in ? -Zi * sc : (T)0;
     }
-    eng.inv2(zr, zi);
+    eng.template inv2<true>(zr, zi);
     const int y = eng.line;
     if (((eng.q | y) & 1) == 0) {
       T* ga = gout + ma * cs + (size_t)cell * N * N + (centered<P>(y) / 2 + N / 2);

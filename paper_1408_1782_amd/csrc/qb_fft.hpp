@@ -21,8 +21,8 @@
 //
 // 2D: rows (index x, line = y) and columns (index y, line = kx).  The field
 // moves between row and column ownership through an LDS transpose, one real
-// component at a time (both at once in workgroups that fill a CU and have
-// the LDS for two planes), through a padded P x P buffer per component.
+// component at a time (both at once where the kernel has the LDS for two
+// planes), through a padded P x P buffer per component.
 //
 //   row real (strided in x) --fwd rows--> row spectra (blocked in kx)
 //     --T1--> column real (strided in y) --fwd cols--> column spectra
@@ -201,6 +201,45 @@ __device__ __forceinline__ double xor_lane(double v) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
+// z += s z(partner lane) for every element.  In float32 one instruction per
+// element (the DPP read is the first source of a v_fmac), written as asm in
+// blocks of eight: the compiler leaves the move and the multiply-add apart.  A
+// DPP read needs two wait states after the VALU write of its register, which
+// nothing outside the asm block guarantees; inside a block every instruction
+// reads a register of its own.
+#define QB_FMAC_DPP8(CTRL)                                                                              \
+  asm("s_nop 1\n\t"                                                                                     \
+      "v_fmac_f32_dpp %0, %0, %8 " CTRL " row_mask:0xf bank_mask:0xf\n\t"                               \
+      "v_fmac_f32_dpp %1, %1, %8 " CTRL " row_mask:0xf bank_mask:0xf\n\t"                               \
+      "v_fmac_f32_dpp %2, %2, %8 " CTRL " row_mask:0xf bank_mask:0xf\n\t"                               \
+      "v_fmac_f32_dpp %3, %3, %8 " CTRL " row_mask:0xf bank_mask:0xf\n\t"                               \
+      "v_fmac_f32_dpp %4, %4, %8 " CTRL " row_mask:0xf bank_mask:0xf\n\t"                               \
+      "v_fmac_f32_dpp %5, %5, %8 " CTRL " row_mask:0xf bank_mask:0xf\n\t"                               \
+      "v_fmac_f32_dpp %6, %6, %8 " CTRL " row_mask:0xf bank_mask:0xf\n\t"                               \
+      "v_fmac_f32_dpp %7, %7, %8 " CTRL " row_mask:0xf bank_mask:0xf"                                    \
+      : "+v"(z[b]), "+v"(z[b + 1]), "+v"(z[b + 2]), "+v"(z[b + 3]), "+v"(z[b + 4]), "+v"(z[b + 5]),     \
+        "+v"(z[b + 6]), "+v"(z[b + 7])                                                                   \
+      : "v"(s))
+template <int MASK, int E>
+__device__ __forceinline__ void add_lanes(float (&z)[E], float s) {
+  static_assert(E % 8 == 0, "blocks of eight");
+#pragma unroll
+  for (int b = 0; b < E; b += 8) {
+    if constexpr (MASK == 1)
+      QB_FMAC_DPP8("quad_perm:[1,0,3,2]");
+    else if constexpr (MASK == 2)
+      QB_FMAC_DPP8("quad_perm:[2,3,0,1]");
+    else
+      QB_FMAC_DPP8("row_half_mirror");
+  }
+}
+#undef QB_FMAC_DPP8
+template <int MASK, int E>
+__device__ __forceinline__ void add_lanes(double (&z)[E], double s) {
+#pragma unroll
+  for (int k = 0; k < E; ++k) z[k] = fma(xor_lane<MASK>(z[k]), s, z[k]);
+}
+
 // ------------------------------------------------------------------ engine
 template <typename T, int P_, int E_, bool XB_ = false>
 struct Fft2 {
@@ -211,25 +250,14 @@ struct Fft2 {
   static constexpr int LB = ilog2(TPR);
   // LDS transpose layout: row kx holds y at y + off(kx), rows LD apart, with
   // off(kx) = (BW / TPR) * (kx / E), BW the number of elements per 128-byte
-  // bank cycle, LD = P + BW + TPR.  Every transpose access of a wavefront then
+  // bank cycle, LD = P + TPR.  Every transpose access of a wavefront then
   // falls into distinct banks, and each thread's E accesses differ by
   // compile-time constants (one address register per direction).
   static constexpr int BW = 128 / (int)sizeof(T);
-  static constexpr int LD = P + BW + TPR;
-  // The transposes can go through LDS in ROUNDS passes of P / ROUNDS kx rows
-  // each (a smaller buffer, at the price of extra barriers and registers);
-  // one pass unless QB_XPOSE_SPLIT_BYTES asks for a split.
-#ifndef QB_XPOSE_SPLIT_BYTES
-#define QB_XPOSE_SPLIT_BYTES (1 << 30)
-#endif
-  static constexpr int ROUNDS = (P * LD * (int)sizeof(T) > QB_XPOSE_SPLIT_BYTES && P / 2 >= E) ? 2 : 1;
-  static constexpr int RP = P / ROUNDS;
-  static constexpr int PLANE = RP * LD;  // one real plane of the transpose buffer
-  // Kernels whose workgroups of 512 threads or more fill a compute unit on
-  // their own (one per CU at their register use) may ask (XB_) to move the
-  // real and imaginary planes together through two buffers: two barriers
-  // per transpose instead of four, where every barrier idles the whole CU.
-  static constexpr bool XB = XB_ && ROUNDS == 1 && NT >= 512 && 2 * PLANE * (int)sizeof(T) <= 96 * 1024;
+  static constexpr int LD = P + TPR;
+  static constexpr int PLANE = P * LD + (TPR - 1) * (BW / TPR);  // one real plane of the transpose buffer
+  // With XB the real and imaginary planes move together through two buffers.
+  static constexpr bool XB = XB_;
   static constexpr int LDS_SCALARS = (XB ? 2 : 1) * PLANE;
   static_assert(TPR >= 1 && TPR <= 8 && (TPR & (TPR - 1)) == 0, "TPR must be 1, 2, 4 or 8");
   static_assert(E * TPR == P, "E * TPR must equal P");
@@ -278,92 +306,94 @@ struct Fft2 {
     }
   }
 
-  // twiddle w_8^r, r = 0..3, of the H = 4 lane stage (conjugated for the
-  // inverse), as (re, im)
+  // Twiddle of the H = 4 lane stage as (re, im): -w_8^r, r = q mod 4, on the
+  // upper lanes (conjugated for the inverse), 1 on the lower ones.
   template <int SG>
-  __device__ __forceinline__ void w8(int r, T& wr, T& wi) const {
+  __device__ __forceinline__ void w8(T& wr, T& wi) const {
     const T c = (T)0.70710678118654752440;
-    wr = r == 0 ? (T)1 : (r == 1 ? c : (r == 2 ? (T)0 : -c));
-    const T s = r == 0 ? (T)0 : (r == 2 ? (T)1 : c);
-    wi = SG < 0 ? -s : s;
+    const int r = q & 3;
+    const T cr = r == 0 ? (T)1 : (r == 1 ? c : (r == 2 ? (T)0 : -c));
+    const T sr = r == 0 ? (T)0 : (r == 2 ? (T)1 : c);
+    wr = (q & 4) ? -cr : (T)1;
+    wi = (q & 4) ? (SG < 0 ? sr : -sr) : (T)0;
   }
 
-  // Cross-lane DFT of size TPR for every k.  Forward (decimation in
-  // frequency, natural lane order in, bit-reversed out):
-  //   stage H = TPR/2 .. 1: lower lane z + o, upper lane (o - z) w_{2H}^{q mod H}
-  // The H = 2 stage twiddle is w_4 = -i (lanes with q mod 4 = 3), applied as a
-  // component swap; the H = 4 stage (TPR = 8) multiplies the upper lanes by
-  // w_8^{q mod 4}.
+  // Cross-lane DFT of size TPR for every k (forward: decimation in frequency,
+  // natural lane order in, bit-reversed out): stage H = TPR/2 .. 1 adds the
+  // partner lane q ^ H, then the upper lanes take the twiddle w_{2H}^{q mod H}.
+  // A stage is z + s z_partner with s = +1 on lower and -1 on upper lanes:
+  // one fused multiply-add whose partner operand is a DPP read (in float32 a
+  // single instruction, 4.3 clocks; a separate move took 4.3 and the add 2.7),
+  // which leaves the upper lanes with the sign reversed.  The twiddles of the
+  // H = 4 stage and the rotation of lane 3 after the H = 2 stage take that
+  // sign up; what is left after the last stage is a factor
+  //   sigma(q) = (-1)^(number of ones in q mod 4)
+  // on the spectrum, which lanes_inv expects and undoes.  Every spectrum the
+  // kernels keep carries it: in two dimensions the entry (kx, ky) has the sign
+  // sigma(lane of kx) sigma(lane of ky).  Tables and phases multiply through;
+  // only a step that mixes k with another frequency has to look (k_grad_pre).
   __device__ __forceinline__ void lanes_fwd(T (&zr)[E], T (&zi)[E]) const {
     if constexpr (TPR == 8) {
       const T sg = (q & 4) ? (T)-1 : (T)1;
       T wr, wi;
-      w8<-1>((q & 4) ? (q & 3) : 0, wr, wi);
+      w8<-1>(wr, wi);
+      add_lanes<7>(zr, sg);
+      add_lanes<7>(zi, sg);
 #pragma unroll
-      for (int k = 0; k < E; ++k) {
-        const T orr = xor_lane<7>(zr[k]), oi = xor_lane<7>(zi[k]);
-        const T dr = sg * zr[k] + orr, di = sg * zi[k] + oi;
-        zr[k] = dr * wr - di * wi;
-        zi[k] = dr * wi + di * wr;
-      }
+      for (int k = 0; k < E; ++k) cmul_by(zr[k], zi[k], wr, wi);
     }
     if constexpr (TPR >= 4) {
       const T sg = (q & 2) ? (T)-1 : (T)1;
       const bool rot = (q & 3) == 3;
+      add_lanes<2>(zr, sg);
+      add_lanes<2>(zi, sg);
 #pragma unroll
       for (int k = 0; k < E; ++k) {
-        const T orr = xor_lane<2>(zr[k]), oi = xor_lane<2>(zi[k]);
-        const T dr = sg * zr[k] + orr, di = sg * zi[k] + oi;
-        zr[k] = rot ? di : dr;       // (d) * (-i) = (d_i, -d_r)
+        const T dr = zr[k], di = zi[k];
+        zr[k] = rot ? di : dr;       // d (-i) = (d_i, -d_r)
         zi[k] = rot ? -dr : di;
       }
     }
     if constexpr (TPR >= 2) {
       const T sg = (q & 1) ? (T)-1 : (T)1;
-#pragma unroll
-      for (int k = 0; k < E; ++k) {
-        const T orr = xor_lane<1>(zr[k]), oi = xor_lane<1>(zi[k]);
-        zr[k] = sg * zr[k] + orr;
-        zi[k] = sg * zi[k] + oi;
-      }
+      add_lanes<1>(zr, sg);
+      add_lanes<1>(zi, sg);
     }
   }
   // exact reverse of lanes_fwd (unnormalized: times TPR)
   __device__ __forceinline__ void lanes_inv(T (&zr)[E], T (&zi)[E]) const {
     if constexpr (TPR >= 2) {
-      const T sg = (q & 1) ? (T)-1 : (T)1;
-#pragma unroll
-      for (int k = 0; k < E; ++k) {
-        const T orr = xor_lane<1>(zr[k]), oi = xor_lane<1>(zi[k]);
-        zr[k] = sg * zr[k] + orr;
-        zi[k] = sg * zi[k] + oi;
-      }
+      const T sg = (q & 1) ? (T)1 : (T)-1;
+      add_lanes<1>(zr, sg);
+      add_lanes<1>(zi, sg);
     }
     if constexpr (TPR >= 4) {
-      const T sg = (q & 2) ? (T)-1 : (T)1;
+      const T sg = (q & 2) ? (T)1 : (T)-1;
       const bool rot = (q & 3) == 3;
 #pragma unroll
       for (int k = 0; k < E; ++k) {
-        // undo the -i of lanes q mod 4 = 3: multiply by +i = (-z_i, z_r)
-        const T ar = rot ? -zi[k] : zr[k];
-        const T ai = rot ? zr[k] : zi[k];
-        const T orr = xor_lane<2>(ar), oi = xor_lane<2>(ai);
-        zr[k] = sg * ar + orr;
-        zi[k] = sg * ai + oi;
+        // z i = (-z_i, z_r) on lane 3
+        const T dr = zr[k], di = zi[k];
+        zr[k] = rot ? -di : dr;
+        zi[k] = rot ? dr : di;
       }
+      add_lanes<2>(zr, sg);
+      add_lanes<2>(zi, sg);
     }
     if constexpr (TPR == 8) {
-      const T sg = (q & 4) ? (T)-1 : (T)1;
+      const T sg = (q & 4) ? (T)1 : (T)-1;
       T wr, wi;
-      w8<+1>((q & 4) ? (q & 3) : 0, wr, wi);
+      w8<+1>(wr, wi);
 #pragma unroll
-      for (int k = 0; k < E; ++k) {
-        const T ar = zr[k] * wr - zi[k] * wi, ai = zr[k] * wi + zi[k] * wr;
-        const T orr = xor_lane<7>(ar), oi = xor_lane<7>(ai);
-        zr[k] = sg * ar + orr;
-        zi[k] = sg * ai + oi;
-      }
+      for (int k = 0; k < E; ++k) cmul_by(zr[k], zi[k], wr, wi);
+      add_lanes<7>(zr, sg);
+      add_lanes<7>(zi, sg);
     }
+  }
+  static __device__ __forceinline__ void cmul_by(T& r, T& i, T c, T s) {
+    const T x = r * c - i * s;
+    i = r * s + i * c;
+    r = x;
   }
 
   // forward: strided -> blocked, exp(-2 pi i ...)
@@ -385,118 +415,68 @@ struct Fft2 {
   }
 
   // T1: row spectra (blocked in kx, line = y) -> column real (strided in y, line = kx)
+  // T2: column real -> row spectra, back along the same addresses.
+  // A thread writes in T1 where it last read in T2 and the other way round, so
+  // a transpose that follows its opposite (OWN) finds the addresses it
+  // writes free: one barrier, between the writes and the reads, with two
+  // planes, three with one.  Otherwise a leading barrier waits for the reads
+  // of the transpose before.
+  template <bool OWN>
   __device__ __forceinline__ void t_rows_to_cols(T (&zr)[E], T (&zi)[E]) const {
-    if constexpr (XB) {
+    auto wr = [&](T* p, const T (&z)[E]) {
 #pragma unroll
-      for (int k = 0; k < E; ++k) {
-        const int a = addr(bk(k), line) + off_of(bk(k));
-        lds[a] = zr[k];
-        lds[PLANE + a] = zi[k];
-      }
-      __syncthreads();
+      for (int k = 0; k < E; ++k) p[addr(bk(k), line) + off_of(bk(k))] = z[k];
+    };
+    auto rd = [&](const T* p, T (&z)[E]) {
 #pragma unroll
-      for (int n = 0; n < E; ++n) {
-        const int a = addr(line, sx(n)) + off_of(line);
-        zr[n] = lds[a];
-        zi[n] = lds[PLANE + a];
-      }
-      __syncthreads();
-    } else {
-      xpose_rb_to_cs(zr);
-      xpose_rb_to_cs(zi);
-    }
+      for (int n = 0; n < E; ++n) z[n] = p[addr(line, sx(n)) + off_of(line)];
+    };
+    move<OWN>(zr, zi, wr, rd);
   }
-  // T2: column real (strided in y, line = kx) -> row spectra (blocked in kx, line = y)
+  template <bool OWN>
   __device__ __forceinline__ void t_cols_to_rows(T (&zr)[E], T (&zi)[E]) const {
+    auto wr = [&](T* p, const T (&z)[E]) {
+#pragma unroll
+      for (int n = 0; n < E; ++n) p[addr(line, sx(n)) + off_of(line)] = z[n];
+    };
+    auto rd = [&](const T* p, T (&z)[E]) {
+#pragma unroll
+      for (int k = 0; k < E; ++k) z[k] = p[addr(bk(k), line) + off_of(bk(k))];
+    };
+    move<OWN>(zr, zi, wr, rd);
+  }
+  template <bool OWN, typename W, typename R>
+  __device__ __forceinline__ void move(T (&zr)[E], T (&zi)[E], W wr, R rd) const {
+    if constexpr (!OWN) __syncthreads();
     if constexpr (XB) {
-#pragma unroll
-      for (int n = 0; n < E; ++n) {
-        const int a = addr(line, sx(n)) + off_of(line);
-        lds[a] = zr[n];
-        lds[PLANE + a] = zi[n];
-      }
+      wr(lds, zr);
+      wr(lds + PLANE, zi);
       __syncthreads();
-#pragma unroll
-      for (int k = 0; k < E; ++k) {
-        const int a = addr(bk(k), line) + off_of(bk(k));
-        zr[k] = lds[a];
-        zi[k] = lds[PLANE + a];
-      }
-      __syncthreads();
+      rd(lds, zr);
+      rd(lds + PLANE, zi);
     } else {
-      xpose_cs_to_rb(zr);
-      xpose_cs_to_rb(zi);
+      wr(lds, zr);
+      __syncthreads();
+      rd(lds, zr);
+      __syncthreads();
+      wr(lds, zi);
+      __syncthreads();
+      rd(lds, zi);
     }
   }
 
-  // With ROUNDS > 1 a thread may receive its column elements in an earlier
-  // round than the one in which it hands over its row elements, so received
-  // values go to a separate array until every round is done.
-  __device__ __forceinline__ void xpose_rb_to_cs(T (&z)[E]) const {
-    if constexpr (ROUNDS == 1) {
-#pragma unroll
-      for (int k = 0; k < E; ++k) lds[addr(bk(k), line) + off_of(bk(k))] = z[k];
-      __syncthreads();
-#pragma unroll
-      for (int n = 0; n < E; ++n) z[n] = lds[addr(line, sx(n)) + off_of(line)];
-      __syncthreads();
-    } else {
-      T zn[E];
-#pragma unroll
-      for (int r = 0; r < ROUNDS; ++r) {
-        if ((E * bq) / RP == r) {
-#pragma unroll
-          for (int k = 0; k < E; ++k) lds[addr(bk(k) - r * RP, line) + off_of(bk(k))] = z[k];
-        }
-        __syncthreads();
-        if (line / RP == r) {
-#pragma unroll
-          for (int n = 0; n < E; ++n) zn[n] = lds[addr(line - r * RP, sx(n)) + off_of(line)];
-        }
-        __syncthreads();
-      }
-#pragma unroll
-      for (int n = 0; n < E; ++n) z[n] = zn[n];
-    }
-  }
-  __device__ __forceinline__ void xpose_cs_to_rb(T (&z)[E]) const {
-    if constexpr (ROUNDS == 1) {
-#pragma unroll
-      for (int n = 0; n < E; ++n) lds[addr(line, sx(n)) + off_of(line)] = z[n];
-      __syncthreads();
-#pragma unroll
-      for (int k = 0; k < E; ++k) z[k] = lds[addr(bk(k), line) + off_of(bk(k))];
-      __syncthreads();
-    } else {
-      T zn[E];
-#pragma unroll
-      for (int r = 0; r < ROUNDS; ++r) {
-        if (line / RP == r) {
-#pragma unroll
-          for (int n = 0; n < E; ++n) lds[addr(line - r * RP, sx(n)) + off_of(line)] = z[n];
-        }
-        __syncthreads();
-        if ((E * bq) / RP == r) {
-#pragma unroll
-          for (int k = 0; k < E; ++k) zn[k] = lds[addr(bk(k) - r * RP, line) + off_of(bk(k))];
-        }
-        __syncthreads();
-      }
-#pragma unroll
-      for (int k = 0; k < E; ++k) z[k] = zn[k];
-    }
-  }
-
-  // full 2D: row real -> column spectra
+  // full 2D: row real -> column spectra (OWN: the last transform was an inv2)
+  template <bool OWN = false>
   __device__ __forceinline__ void fwd2(T (&zr)[E], T (&zi)[E]) const {
     fwd_line(zr, zi);
-    t_rows_to_cols(zr, zi);
+    t_rows_to_cols<OWN>(zr, zi);
     fwd_line(zr, zi);
   }
-  // full 2D: column spectra -> row real
+  // full 2D: column spectra -> row real (OWN: the last transform was a fwd2)
+  template <bool OWN = false>
   __device__ __forceinline__ void inv2(T (&zr)[E], T (&zi)[E]) const {
     inv_line(zr, zi);
-    t_cols_to_rows(zr, zi);
+    t_cols_to_rows<OWN>(zr, zi);
     inv_line(zr, zi);
   }
 };

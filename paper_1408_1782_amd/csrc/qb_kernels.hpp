@@ -222,7 +222,12 @@ __global__ void k_state_to_api(const T* __restrict__ w, TA* __restrict__ W, int 
 }
 
 // ------------------------------------------------------------------ engine setup
-template <typename T, int P, int E, bool XB = false>
+// Whether the LDS of a compute unit holds two planes of the transpose buffer
+// (all but float64 at P = 128).
+template <typename T, int P, int E>
+constexpr bool two_planes = (2 * Fft2<T, P, E>::PLANE + Fft2<T, P, E>::TW_SCALARS) * (int)sizeof(T) <= 160 * 1024;
+
+template <typename T, int P, int E, bool XB = two_planes<T, P, E>>
 struct Kern {
   using Eng = Fft2<T, P, E, XB>;
   static constexpr int NT = Eng::NT;
@@ -231,7 +236,10 @@ struct Kern {
   static constexpr int LDS = Eng::LDS_SCALARS + Eng::TW_SCALARS;
   // least occupancy of k_i3 (waves per SIMD): two workgroups of 256 threads
   // per compute unit, which a few registers more than 256 would halve
-  static constexpr int WAVES = 1;
+  // least occupancy of k_i3 (waves per SIMD): at P = 64, E = 8 in float32 two
+  // workgroups of 512 threads per compute unit (10.1 ms at N = 32 over 128
+  // cells; 12.4 with the few registers more that leave room for one)
+  static constexpr int WAVES = NT == 512 && sizeof(T) == 4 && P == 64 ? 4 : 1;
 };
 
 template <typename T, int P, int E, bool XB>
@@ -262,6 +270,11 @@ struct I3Regs {
   static constexpr int BUDGET = 512 / WPS < 256 ? 512 / WPS : 256;
   static constexpr int F = E * (int)sizeof(T) / 4;  // VGPRs of one field
   static constexpr bool PAIR = 2 * F + 2 * F + 48 <= BUDGET;
+  // whether the I_3 kernels move both planes of a transpose at once, or leave
+  // the LDS to accumulators (P = 64 with E = 16 in float32: three of them) and
+  // staging (P = 128); measured at P = 64, E = 16: float64 24.3 ms with two
+  // planes and 26.6 with one and an accumulator, float32 11.7 and 10.8
+  static constexpr bool XB = P == 32 || (P == 64 && (NT >= 512 || sizeof(T) == 8));
   // the transforms need about 2 E more values of temporaries once the
   // shifted fields live in registers too
   template <bool PR>
@@ -283,8 +296,9 @@ struct I3Regs {
   // through memory at every node.
   template <bool PR, int LDS_SCALARS>
   static constexpr int lds_acc() {
-    if (!PR || P != 64 || NT != 256) return 0;
-    const int k = (80 * 1024 - LDS_SCALARS * (int)sizeof(T)) / (P * P * (int)sizeof(T));
+    if (!PR || P != 64 || NT < 256) return 0;
+    const int per = NT == 512 && sizeof(T) == 8 ? 160 : 80;
+    const int k = (per * 1024 - LDS_SCALARS * (int)sizeof(T)) / (P * P * (int)sizeof(T));
     return k < 0 ? 0 : (k > 4 ? 4 : k);
   }
 };
@@ -300,7 +314,7 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_dft_in(DevPlan<T> d, co
   using K = Kern<T, P, E>;
   constexpr unsigned S = sizeof(T);
   __shared__ T smem[K::LDS];
-  Fft2<T, P, E> eng;
+  typename K::Eng eng;
   setup(eng, smem, d.tw);
   const int lc = blockIdx.x >> 2, mu = blockIdx.x & 3;
   const int cell = cell0 + lc;
@@ -322,7 +336,7 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_dft_in(DevPlan<T> d, co
     zr[n] = on_grid ? wrow[vel_index<P, K::TPR>(eng.q, n) * N] : (T)0;
     zi[n] = 0;
   }
-  eng.fwd2(zr, zi);
+  eng.template fwd2<true>(zr, zi);
 #pragma unroll
   for (int k = 0; k < E; ++k) {
     const int by = centered<P>(eng.bk(k));
@@ -332,7 +346,7 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_dft_in(DevPlan<T> d, co
     bst<T>(rs, zr[k], vo, ((2 * mu) * K::FSZ + k * K::NT) * S);
     bst<T>(rs, zi[k], vo, ((2 * mu + 1) * K::FSZ + k * K::NT) * S);
   }
-  eng.inv2(zr, zi);
+  eng.template inv2<true>(zr, zi);
 #pragma unroll
   for (int n = 0; n < E; ++n) {
     const unsigned o = n * K::NT;
@@ -362,7 +376,7 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_terms(DevPlan<T> d, int
   constexpr unsigned S = sizeof(T);
   constexpr bool TREG = I3Regs<T, P, E>::PAIR;
   __shared__ T smem[K::LDS];
-  Fft2<T, P, E> eng;
+  typename K::Eng eng;
   setup(eng, smem, d.tw);
   // one (cell, task, group) per workgroup, or grid-stride when persistent
   const int per_cell = kTermPlanes * d.tg;
@@ -378,6 +392,7 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_terms(DevPlan<T> d, int
   const rsrc_t ro = mkbuf(d.terms + (size_t)pt * K::FSZ, K::FSZ);
   const size_t tabn = (size_t)d.J * K::FSZ;
   if (task < 7) {
+    __syncthreads();  // the transposes of the task before have been read
     const int g = task < 3 ? task + 1 : task - 3;
     const rsrc_t rin = mkbuf(task < 3 ? d.phip : d.psip, tabn);
     const rsrc_t rout = mkbuf(task < 3 ? d.Kt : d.psiw, tabn);
@@ -410,14 +425,14 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_terms(DevPlan<T> d, int
         zr[k] = wr * cr - wi * ci;
         zi[k] = wr * ci + wi * cr;
       }
-      eng.inv2(zr, zi);
+      eng.template inv2<true>(zr, zi);
 #pragma unroll
       for (int n = 0; n < E; ++n) {
         const T f = bld<T>(rw, vo, (4 * K::FSZ + n * K::NT) * S);
         zr[n] *= f;
         zi[n] *= f;
       }
-      eng.fwd2(zr, zi);
+      eng.template fwd2<true>(zr, zi);
 #pragma unroll
       for (int k = 0; k < E; ++k) {
         const unsigned o = k * K::NT;
@@ -442,7 +457,7 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_terms(DevPlan<T> d, int
       zr[k] = TREG ? sr[TREG ? k : 0] : bld<T>(ra, vo, o * S);
       zi[k] = TREG ? si[TREG ? k : 0] : bld<T>(ra, vo, (K::FSZ + o) * S);
     }
-    eng.inv2(zr, zi);
+    eng.template inv2<true>(zr, zi);
 #pragma unroll
     for (int n = 0; n < E; ++n) bst<T>(ro, zr[n], vo, (n * K::NT) * S);
   } else {
@@ -516,7 +531,7 @@ __device__ __forceinline__ T pick4(int i, T a, T b, T c, T d) {
 
 template <typename T, int P, int E, bool PAIR>
 __global__ __launch_bounds__((Fft2<T, P, E>::NT)) __attribute__((amdgpu_waves_per_eu(Kern<T, P, E>::WAVES))) void k_i3(DevPlan<T> d, int ncells) {
-  using K = Kern<T, P, E, true>;
+  using K = Kern<T, P, E, I3Regs<T, P, E>::XB>;
   constexpr unsigned S = sizeof(T);
   constexpr bool SREG = I3Regs<T, P, E>::template sreg<PAIR>();
   // Paired nodes keep the partner sums of a row pair in registers where the
@@ -527,11 +542,9 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) __attribute__((amdgpu_waves_pe
   constexpr bool PMEM = PAIR && !PREG;
   static_assert(!(PMEM && SREG), "partner sums in memory need the shifted-field buffer");
   // the current row pair's two shifted fields in registers for the nu loop
-  // (saves two field reads per convolution), with at most 16 registers per
-  // field: it fits the unpaired kernel; in the paired float32 kernel at
-  // P = 128 it pushes about 38 registers to scratch and still runs 4 %
-  // faster, the field reads it saves waiting right after a transform
-  constexpr bool AREG = !SREG && I3Regs<T, P, E>::F <= 16;
+  // (saves two field reads per convolution) where 16 registers per field do
+  // not cost the batches below their registers
+  constexpr bool AREG = !SREG && P <= 64 && I3Regs<T, P, E>::F <= 16;
   // PF: the accumulator field read back after a convolution is fetched
   // into LDS (buffer-to-LDS loads, no registers) before the convolution
   // starts, so its latency hides behind the transforms
@@ -542,9 +555,17 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) __attribute__((amdgpu_waves_pe
   // own elements, so no barrier guards them
   constexpr int KRES = I3Regs<T, P, E>::template lds_acc<PAIR, K::LDS>();
   __shared__ T acc[KRES > 0 ? KRES * K::FSZ : 1];
-  // elements between scheduling barriers in the element loops, which bound
-  // the loads in flight (measured: 4 at P = 128, 8 at P = 64)
+  // Elements whose loads are in flight together, in the loops that form the
+  // shifted fields and the products (SG), multiply by psi' (SM), use up a
+  // convolution (SB) and accumulate the partner spectra (PB): as many as the
+  // registers beside the transform operand hold.  In float32 at P = 128 with
+  // SB = 4 and no row registers 60.5 ms over 64 cells (N = 64), 65.8 with the
+  // rows in registers and 37 spilled, 74.4 one element at a time; one step
+  // more of any of them spills (SB = 8: 62 to 63).
   constexpr int SG = P >= 128 ? 4 : 8;
+  constexpr int SM = PMEM ? 4 : 8;
+  constexpr int SB = PMEM ? 2 : 4;
+  constexpr int PB = PMEM ? 1 : 8;
   const unsigned tid = threadIdx.x;
   typename K::Eng eng;
   setup(eng, smem, d.tw);
@@ -653,15 +674,15 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) __attribute__((amdgpu_waves_pe
           zi[n] = bld<T>(rw, vo, (m1 * K::FSZ + o) * S) * sv;
           if (n % SG == SG - 1) __builtin_amdgcn_sched_barrier(0);
         }
-        eng.fwd2(zr, zi);
+        eng.template fwd2<true>(zr, zi);
 #pragma unroll
         for (int k = 0; k < E; ++k) {
           const T a = bld<T>(rm, vo, (k * K::NT) * S);
           zr[k] *= a;
           zi[k] *= a;
-          if (k % SG == SG - 1) __builtin_amdgcn_sched_barrier(0);
+          if (k % SM == SM - 1) __builtin_amdgcn_sched_barrier(0);
         }
-        eng.inv2(zr, zi);
+        eng.template inv2<true>(zr, zi);
         const T e0 = m0 == 0 ? wgt : -wgt;
         // c eta_nu, zero for the middle node of an odd M (no partner): the
         // partner sums then take zeros instead of a branch per element
@@ -669,47 +690,65 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) __attribute__((amdgpu_waves_pe
         const unsigned pt = PF ? lds_fetch_wait() : 0u;
         const bool res = KRES > 0 && nu < KRES;
         T* const al = acc + (KRES > 0 && res ? nu * K::FSZ : 0) + tid;
+        // in batches of SB elements, every load of a batch before its first
+        // store: the compiler keeps buffer loads behind earlier buffer
+        // stores, so loads and stores element by element would wait for
+        // memory once per element.
 #pragma unroll
-        for (int n = 0; n < E; ++n) {
-          const unsigned o = n * K::NT;
-          T sa, sb;
-          if constexpr (SREG) {
-            sa = mp == 0 ? s[0][n] : s[SREG ? 2 : 0][n];
-            sb = mp == 0 ? s[SREG ? 1 : 0][n] : s[SREG ? 3 : 0][n];
-          } else if constexpr (AREG) {
-            sa = ra[AREG ? n : 0];
-            sb = rbv[AREG ? n : 0];
-          } else {
-            sa = bld<T>(rb, vo, (m0 * K::FSZ + o) * S);
-            sb = bld<T>(rb, vo, (m1 * K::FSZ + o) * S);
+        for (int b = 0; b < E; b += SB) {
+          T sa[SB], sb[SB], prev[SB], wv[SB], pva[PMEM ? SB : 1], pvb[PMEM ? SB : 1];
+#pragma unroll
+          for (int i = 0; i < SB; ++i) {
+            const int n = b + i;
+            const unsigned o = n * K::NT;
+            if constexpr (PAIR) wv[i] = bld<T>(rw, vo, (nu * K::FSZ + o) * S);
+            if constexpr (PMEM) {
+              pva[PMEM ? i : 0] = bld<T>(rb, vo, (4 * K::FSZ + o) * S);
+              pvb[PMEM ? i : 0] = bld<T>(rb, vo, (5 * K::FSZ + o) * S);
+            }
+            if constexpr (SREG) {
+              sa[i] = mp == 0 ? s[0][n] : s[SREG ? 2 : 0][n];
+              sb[i] = mp == 0 ? s[SREG ? 1 : 0][n] : s[SREG ? 3 : 0][n];
+            } else if constexpr (AREG) {
+              sa[i] = ra[AREG ? n : 0];
+              sb[i] = rbv[AREG ? n : 0];
+            } else {
+              sa[i] = bld<T>(rb, vo, (m0 * K::FSZ + o) * S);
+              sb[i] = bld<T>(rb, vo, (m1 * K::FSZ + o) * S);
+            }
+            // the accumulator is read on the first pass too (in bounds, not
+            // yet written) and the value dropped by a select
+            if constexpr (PF)
+              prev[i] = pf[PF ? o + pt : 0];
+            else if (!(KRES > 0 && res))
+              prev[i] = bld<T>(ro, vo, (nu * K::FSZ + o) * S);
           }
-          const unsigned off = (nu * K::FSZ + o) * S;
-          T v = e0 * sa * zr[n] - wgt * sb * zi[n];
-          // the accumulator is read on the first pass too (in bounds, not
-          // yet written) and the value dropped by a select: uniform branches
-          // here would cut the element loop into separately scheduled blocks
-          if (KRES > 0 && res) {
-            const T prev = al[KRES > 0 ? o : 0];
-            v += first ? (T)0 : prev;
-            al[KRES > 0 ? o : 0] = v;
-          } else {
-            const T prev = PF ? pf[PF ? o + pt : 0] : bld<T>(ro, vo, off);
-            v += first ? (T)0 : prev;
-            bst<T>(ro, v, vo, off);
+          if constexpr (SB > 1) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int i = 0; i < SB; ++i) {
+            const int n = b + i;
+            const unsigned o = n * K::NT;
+            T v = e0 * sa[i] * zr[n] - wgt * sb[i] * zi[n];
+            if (KRES > 0 && res) {
+              const T pl = al[KRES > 0 ? o : 0];
+              v += first ? (T)0 : pl;
+              al[KRES > 0 ? o : 0] = v;
+            } else {
+              v += first ? (T)0 : prev[i];
+              bst<T>(ro, v, vo, (nu * K::FSZ + o) * S);
+            }
+            if constexpr (PREG) {
+              const T we = ew * wv[i];
+              pa[PREG ? n : 0] += sa_sign * we * zr[n];
+              pb[PREG ? n : 0] += we * zi[n];
+            } else if constexpr (PMEM) {
+              // first nu of the row pair: the old value is dropped by a select
+              const T we = ew * wv[i];
+              bst<T>(rb, sa_sign * we * zr[n] + (nu != 0 ? pva[PMEM ? i : 0] : (T)0), vo, (4 * K::FSZ + o) * S);
+              bst<T>(rb, we * zi[n] + (nu != 0 ? pvb[PMEM ? i : 0] : (T)0), vo, (5 * K::FSZ + o) * S);
+            }
           }
-          if constexpr (PREG) {
-            const T wv = ew * bld<T>(rw, vo, (nu * K::FSZ + o) * S);
-            pa[PREG ? n : 0] += sa_sign * wv * zr[n];
-            pb[PREG ? n : 0] += wv * zi[n];
-          } else if constexpr (PMEM) {
-            // first nu of the row pair: the old value is dropped by a select
-            const T wv = ew * bld<T>(rw, vo, (nu * K::FSZ + o) * S);
-            const unsigned qa = (4 * K::FSZ + o) * S, qb = (5 * K::FSZ + o) * S;
-            const T pva = bld<T>(rb, vo, qa), pvb = bld<T>(rb, vo, qb);
-            bst<T>(rb, sa_sign * wv * zr[n] + (nu != 0 ? pva : (T)0), vo, qa);
-            bst<T>(rb, wv * zi[n] + (nu != 0 ? pvb : (T)0), vo, qb);
-          }
-          if (n % SG == SG - 1) __builtin_amdgcn_sched_barrier(0);
+          if ((b + SB) % SG == 0) __builtin_amdgcn_sched_barrier(0);
         }
       }
       // spectrum of the partner sums: conj(phase) fwd2(pa + i pb), accumulated on Xi
@@ -726,22 +765,31 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) __attribute__((amdgpu_waves_pe
             zi[n] = pb[PREG ? n : 0];
           }
         }
-        eng.fwd2(zr, zi);
+        eng.template fwd2<true>(zr, zi);
+        __syncthreads();  // read before the next row pair's transposes write
 #pragma unroll
-        for (int k = 0; k < E; ++k) {
-          const unsigned o = k * K::NT;
-          const unsigned vk = xi_off(k);
-          T er, ei;
-          cmul(pxr, pxi, py[2 * k], py[2 * k + 1], er, ei);
-          T xr, xi;
-          cmul(zr[k], zi[k], er, -ei, xr, xi);
-          const T pr0 = bld<T>(rp, vk, (fr + o) * S);
-          const T pi0 = bld<T>(rp, vk, (fi + o) * S);
-          xr += m != mb ? pr0 : (T)0;
-          xi += m != mb ? pi0 : (T)0;
-          bst<T>(rp, xr, vk, (fr + o) * S);
-          bst<T>(rp, xi, vk, (fi + o) * S);
-          if (k % SG == SG - 1) __builtin_amdgcn_sched_barrier(0);
+        for (int b = 0; b < E; b += PB) {
+          T pr0[PB], pi0[PB];
+#pragma unroll
+          for (int i = 0; i < PB; ++i) {
+            const unsigned o = (b + i) * K::NT, vk = xi_off(b + i);
+            pr0[i] = bld<T>(rp, vk, (fr + o) * S);
+            pi0[i] = bld<T>(rp, vk, (fi + o) * S);
+          }
+#pragma unroll
+          for (int i = 0; i < PB; ++i) {
+            const int k = b + i;
+            const unsigned o = k * K::NT, vk = xi_off(k);
+            T er, ei;
+            cmul(pxr, pxi, py[2 * k], py[2 * k + 1], er, ei);
+            T xr, xi;
+            cmul(zr[k], zi[k], er, -ei, xr, xi);
+            xr += m != mb ? pr0[i] : (T)0;
+            xi += m != mb ? pi0[i] : (T)0;
+            bst<T>(rp, xr, vk, (fr + o) * S);
+            bst<T>(rp, xi, vk, (fi + o) * S);
+          }
+          __builtin_amdgcn_sched_barrier(0);
         }
       } else if (m == mb) {
         // no partner spectrum (unpaired kernel, or a single node)
@@ -883,7 +931,7 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_combine(DevPlan<T> d, T
   using K = Kern<T, P, E>;
   constexpr unsigned S = sizeof(T);
   __shared__ T smem[K::LDS];
-  Fft2<T, P, E> eng;
+  typename K::Eng eng;
   setup(eng, smem, d.tw);
   const int lc = blockIdx.x >> 1, pr = blockIdx.x & 1;
   const int cell = cell0 + lc;
@@ -900,7 +948,7 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_combine(DevPlan<T> d, T
       zr[n] = bld<T>(r3, vo, ((2 * pr) * K::FSZ + o) * S);
       zi[n] = bld<T>(r3, vo, ((2 * pr + 1) * K::FSZ + o) * S);
     }
-    eng.fwd2(zr, zi);
+    eng.template fwd2<true>(zr, zi);
     const int bx = centered<P>(eng.line);
     const bool kx_in = bx > -N / 2 && bx < N / 2;
     const T sc = (T)1 / (T)(P * P);
@@ -914,7 +962,7 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_combine(DevPlan<T> d, T
       zr[k] = in ? (zr[k] + tp * ar) * sc : (T)0;
       zi[k] = in ? (zi[k] + tp * ai) * sc : (T)0;
     }
-    eng.inv2(zr, zi);
+    eng.template inv2<true>(zr, zi);
     const int y = eng.line;
     if (((eng.q | y) & 1) == 0) {
       T* ca = c + (2 * pr) * cs + (size_t)cell * N * N + (centered<P>(y) / 2 + N / 2);

@@ -203,11 +203,20 @@ bool fill_layout_tables(qb_plan_s* pl, qb_plan_s::TabSet& ts) {
       }
     }
   }
-  // col spec position of -k (mod P) for each position of k
+  // col spec position of -k (mod P) for each position of k, with the top bit
+  // set where the kept spectra carry different signs at k and -k
+  const int lb = qb::ilog2(TPR);
+  auto sign = [&](int kx, int ky) {
+    auto ones = [&](int k) { const int q = qb::bitrev_rt(k / E, lb); return (q ^ (q >> 1)) & 1; };
+    return ones(kx) ^ ones(ky);
+  };
   std::vector<unsigned> negk(FSZ);
   for (int kx = 0; kx < P; ++kx)
-    for (int ky = 0; ky < P; ++ky)
-      negk[colspec_index(kx, ky, E, TPR, NT)] = (unsigned)colspec_index((P - kx) % P, (P - ky) % P, E, TPR, NT);
+    for (int ky = 0; ky < P; ++ky) {
+      const int nx = (P - kx) % P, ny = (P - ky) % P;
+      const unsigned flip = sign(kx, ky) != sign(nx, ny) ? 0x80000000u : 0u;
+      negk[colspec_index(kx, ky, E, TPR, NT)] = (unsigned)colspec_index(nx, ny, E, TPR, NT) | flip;
+    }
   ts.built = put<T>(ts.tw, tw) && put<T>(ts.phip, phip) && put<T>(ts.Kt, Kt) && put<T>(ts.psi, psi) &&
              put<T>(ts.psip, psip) && put<T>(ts.psiw, psiw) && put<T>(ts.psips, psips) &&
              hip_ok(hipMemcpy(ts.negk, negk.data(), FSZ * sizeof(unsigned), hipMemcpyHostToDevice), "hipMemcpy");
