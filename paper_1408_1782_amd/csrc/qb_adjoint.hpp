@@ -71,7 +71,7 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_lam_in(DevPlan<T> d, co
   __shared__ T smem[K::LDS];
   typename K::Eng eng;
   setup(eng, smem, d.tw);
-  const int lc = blockIdx.x;
+  const int lc = blockIdx.x >> 1, pr = blockIdx.x & 1;
   const int cell = cell0 + lc;
   const int N = P / 2;
   const unsigned vo = threadIdx.x * S;
@@ -83,8 +83,7 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_lam_in(DevPlan<T> d, co
   const int bx = centered<P>(eng.line);
   const bool kx_in = bx > -N / 2 && bx < N / 2;
   const T sc = (T)1 / (T)(P * P);
-#pragma unroll 1
-  for (int pr = 0; pr < 2; ++pr) {
+  {
     T zr[E], zi[E];
     const T* la = lam + (2 * pr) * cs + (size_t)cell * N * N + (centered<P>(y) / 2 + N / 2);
     const T* lb = la + cs;
@@ -123,7 +122,8 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_lam_in(DevPlan<T> d, co
 //   acot[12..15] the explicit dependence of r on w_mu
 // Part 0 writes acot[0..11], which need only lam and w; part 1 writes
 // acot[12..15] from the forward fields g, y (terms[0..6]) and S (the sum
-// of its per-component parts terms[7..10]), which k_terms_vjp produces.
+// of its per-component parts terms[7..10]), which k_terms_vjp produces, one
+// share per group of directions.
 template <typename T>
 __global__ void k_assemble_vjp(DevPlan<T> d, int ncells, int fsz, int part) {
   const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -151,10 +151,14 @@ __global__ void k_assemble_vjp(DevPlan<T> d, int ncells, int fsz, int part) {
     o[11 * fsz] = tp * l3;
     return;
   }
-  const T* tr = d.terms + cell * kTermPlanes * fsz + e;
-  const T g1 = tr[0], g2 = tr[fsz], g3 = tr[2 * fsz];
-  const T y0 = tr[3 * fsz], y1 = tr[4 * fsz], y2 = tr[5 * fsz], y3 = tr[6 * fsz];
-  const T Sv = (tr[7 * fsz] + tr[8 * fsz]) + (tr[9 * fsz] + tr[10 * fsz]);
+  T t[kTermPlanes];
+  for (int f = 0; f < kTermPlanes; ++f) {
+    const T* tr = d.terms + (cell * kTermPlanes + f) * d.tg * fsz + e;
+    t[f] = tr[0];
+    for (int g = 1; g < d.tg; ++g) t[f] += tr[(size_t)g * fsz];
+  }
+  const T g1 = t[0], g2 = t[1], g3 = t[2], y0 = t[3], y1 = t[4], y2 = t[5], y3 = t[6];
+  const T Sv = (t[7] + t[8]) + (t[9] + t[10]);
   const T q = pi * (-two * Sv + two * y0);
   o[12 * fsz] = q * l0 - tp * (y1 * l1 + y2 * l2 + y3 * l3);
   o[13 * fsz] = -tp * y1 * l0 + q * l1 - two * g3 * l2 + two * g2 * l3;
@@ -163,7 +167,8 @@ __global__ void k_assemble_vjp(DevPlan<T> d, int ncells, int fsz, int part) {
 }
 
 // ------------------------------------------------------------------ I_1, I_4, I_2
-// Transpose of k_terms, one workgroup per (cell, task), fused with the
+// Transpose of k_terms, one workgroup per (cell, task, group of d.td
+// directions; the gathering kernels add the groups), fused with the
 // forward fields the transpose of the assembly needs (k_terms computes
 // the same fields; running both here shares their inner transforms).
 // Tasks 0..6 (I_1 with l = task + 1, I_4 with g = task - 3), per direction j:
@@ -200,8 +205,12 @@ __attribute__((amdgpu_waves_per_eu(Fft2<T, P, E>::NT >= 512 ? 4 : 1))) void k_te
   __shared__ T smem[K::LDS];
   typename K::Eng eng;
   setup(eng, smem, d.tw);
-  const int cell = blockIdx.x / kTermsVjpTasks;
-  const int task = blockIdx.x % kTermsVjpTasks;
+  constexpr int TB = 4;
+  // (cell, task, group of directions), as in k_terms
+  const int ct = blockIdx.x / d.tg, grp = blockIdx.x % d.tg;
+  const int cell = ct / kTermsVjpTasks;
+  const int task = ct % kTermsVjpTasks;
+  const int j0 = grp * d.td, j1 = min(d.J, j0 + d.td);
   const unsigned vo = threadIdx.x * S;
   const rsrc_t rs = mkbuf(d.spec + (size_t)cell * 8 * K::FSZ, 8 * K::FSZ);
   const rsrc_t rw = mkbuf(d.wP + (size_t)cell * 5 * K::FSZ, 5 * K::FSZ);
@@ -212,11 +221,11 @@ __attribute__((amdgpu_waves_per_eu(Fft2<T, P, E>::NT >= 512 ? 4 : 1))) void k_te
     const bool odd = task < 3;
     const rsrc_t rin = mkbuf(odd ? d.phip : d.psip, tabn);
     const rsrc_t rout = mkbuf(odd ? d.Kt : d.psiw, tabn);
-    const rsrc_t rd = mkbuf(d.acc + ((size_t)cell * 7 + task) * 2 * K::FSZ, 2 * K::FSZ);
-    const rsrc_t rc = mkbuf(d.fwa + ((size_t)cell * 7 + task) * 2 * K::FSZ, 2 * K::FSZ);
-    const rsrc_t rf = mkbuf(d.gf0 + ((size_t)cell * 7 + task) * K::FSZ, K::FSZ);
-    const rsrc_t rg = mkbuf(d.gspec + ((size_t)cell * 11 + task) * 2 * K::FSZ, 2 * K::FSZ);
-    const rsrc_t ro = mkbuf(d.terms + ((size_t)cell * kTermPlanes + task) * K::FSZ, K::FSZ);
+    const rsrc_t rd = mkbuf(d.acc + (((size_t)cell * 7 + task) * d.tg + grp) * 2 * K::FSZ, 2 * K::FSZ);
+    const rsrc_t rc = mkbuf(d.fwa + (((size_t)cell * 7 + task) * d.tg + grp) * 2 * K::FSZ, 2 * K::FSZ);
+    const rsrc_t rf = mkbuf(d.gf0 + (((size_t)cell * 7 + task) * d.tg + grp) * K::FSZ, K::FSZ);
+    const rsrc_t rg = mkbuf(d.gspec + (((size_t)cell * 11 + task) * d.tg + grp) * 2 * K::FSZ, 2 * K::FSZ);
+    const rsrc_t ro = mkbuf(d.terms + (size_t)blockIdx.x * K::FSZ, K::FSZ);
     const unsigned fg = 2 * g * K::FSZ;
     const T sgn = odd ? (T)-1 : (T)1;
     {
@@ -235,7 +244,7 @@ __attribute__((amdgpu_waves_per_eu(Fft2<T, P, E>::NT >= 512 ? 4 : 1))) void k_te
       }
     }
 #pragma unroll 1
-    for (int j = 0; j < d.J; j += 2) {
+    for (int j = j0; j < j1; j += 2) {
       const unsigned t1 = j * K::FSZ, t2 = t1 + K::FSZ;
       // B stays in registers for its two uses (some go to scratch under the
       // 128-register cap; measured 4 % faster than a per-task buffer)
@@ -267,32 +276,53 @@ __attribute__((amdgpu_waves_per_eu(Fft2<T, P, E>::NT >= 512 ? 4 : 1))) void k_te
         zi[k] = sr * ci + si * cr;
       }
       eng.inv2(zr, zi);
+      // batches of TB elements, all loads before the first store (see k_i3;
+      // without the scheduling barrier between them up to 200 registers
+      // spill); a value not yet written is read too and dropped by a select
 #pragma unroll
-      for (int n = 0; n < E; ++n) {
-        const unsigned o = n * K::NT;
-        const T br = Br[n], bi = Bi[n];
-        const T f0 = bld<T>(rw, vo, (4 * K::FSZ + o) * S);
-        T fb = sgn * (zr[n] * br + zi[n] * bi);
-        if (j != 0) fb += bld<T>(rf, vo, o * S);
-        bst<T>(rf, fb, vo, o * S);
-        // forward: f0 A, transformed by fwd2 below
-        zr[n] *= f0;
-        zi[n] *= f0;
+      for (int n0 = 0; n0 < E; n0 += TB) {
+        T f0[TB], old[TB];
+#pragma unroll
+        for (int i = 0; i < TB; ++i) {
+          const unsigned o = (n0 + i) * K::NT;
+          f0[i] = bld<T>(rw, vo, (4 * K::FSZ + o) * S);
+          old[i] = bld<T>(rf, vo, o * S);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < TB; ++i) {
+          const int n = n0 + i;
+          const T fb = sgn * (zr[n] * Br[n] + zi[n] * Bi[n]);
+          bst<T>(rf, fb + (j != j0 ? old[i] : (T)0), vo, n * K::NT * S);
+          // forward: f0 A, transformed by fwd2 below
+          zr[n] *= f0[i];
+          zi[n] *= f0[i];
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
       // the pair's forward contribution cout fwd2(f0 A)
       eng.template fwd2<true>(zr, zi);
 #pragma unroll
-      for (int k = 0; k < E; ++k) {
-        const unsigned o = k * K::NT;
-        const T o1 = bld<T>(rout, vo, (t1 + o) * S), o2 = bld<T>(rout, vo, (t2 + o) * S);
-        const T cr = odd ? o2 : o1, ci = odd ? o1 : -o2;
-        T ar = cr * zr[k] - ci * zi[k], ai = cr * zi[k] + ci * zr[k];
-        // read at j = 0 too (not yet written) and dropped by a select
-        const T pr = bld<T>(rc, vo, o * S), pi = bld<T>(rc, vo, (K::FSZ + o) * S);
-        ar += j != 0 ? pr : (T)0;
-        ai += j != 0 ? pi : (T)0;
-        bst<T>(rc, ar, vo, o * S);
-        bst<T>(rc, ai, vo, (K::FSZ + o) * S);
+      for (int k0 = 0; k0 < E; k0 += TB) {
+        T o1[TB], o2[TB], pr[TB], pi[TB];
+#pragma unroll
+        for (int i = 0; i < TB; ++i) {
+          const unsigned o = (k0 + i) * K::NT;
+          o1[i] = bld<T>(rout, vo, (t1 + o) * S);
+          o2[i] = bld<T>(rout, vo, (t2 + o) * S);
+          pr[i] = bld<T>(rc, vo, o * S);
+          pi[i] = bld<T>(rc, vo, (K::FSZ + o) * S);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < TB; ++i) {
+          const int k = k0 + i;
+          const unsigned o = k * K::NT;
+          const T cr = odd ? o2[i] : o1[i], ci = odd ? o1[i] : -o2[i];
+          bst<T>(rc, cr * zr[k] - ci * zi[k] + (j != j0 ? pr[i] : (T)0), vo, o * S);
+          bst<T>(rc, cr * zi[k] + ci * zr[k] + (j != j0 ? pi[i] : (T)0), vo, (K::FSZ + o) * S);
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
       // Z = fwd2(f0 B);  H += cw conj(Z)
 #pragma unroll
@@ -304,17 +334,26 @@ __attribute__((amdgpu_waves_per_eu(Fft2<T, P, E>::NT >= 512 ? 4 : 1))) void k_te
       }
       eng.fwd2(zr, zi);
 #pragma unroll
-      for (int k = 0; k < E; ++k) {
-        const unsigned o = k * K::NT;
-        const T i1 = bld<T>(rin, vo, (t1 + o) * S), i2 = bld<T>(rin, vo, (t2 + o) * S);
-        const T cr = odd ? -i2 : i1, ci = odd ? i1 : i2;
-        T xr = cr * zr[k] + ci * zi[k], xi = ci * zr[k] - cr * zi[k];
-        if (j != 0) {
-          xr += bld<T>(rg, vo, o * S);
-          xi += bld<T>(rg, vo, (K::FSZ + o) * S);
+      for (int k0 = 0; k0 < E; k0 += TB) {
+        T i1[TB], i2[TB], gr[TB], gi[TB];
+#pragma unroll
+        for (int i = 0; i < TB; ++i) {
+          const unsigned o = (k0 + i) * K::NT;
+          i1[i] = bld<T>(rin, vo, (t1 + o) * S);
+          i2[i] = bld<T>(rin, vo, (t2 + o) * S);
+          gr[i] = bld<T>(rg, vo, o * S);
+          gi[i] = bld<T>(rg, vo, (K::FSZ + o) * S);
         }
-        bst<T>(rg, xr, vo, o * S);
-        bst<T>(rg, xi, vo, (K::FSZ + o) * S);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < TB; ++i) {
+          const int k = k0 + i;
+          const unsigned o = k * K::NT;
+          const T cr = odd ? -i2[i] : i1[i], ci = odd ? i1[i] : i2[i];
+          bst<T>(rg, cr * zr[k] + ci * zi[k] + (j != j0 ? gr[i] : (T)0), vo, o * S);
+          bst<T>(rg, ci * zr[k] - cr * zi[k] + (j != j0 ? gi[i] : (T)0), vo, (K::FSZ + o) * S);
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
     // the forward field: Re inv2(sum over pairs)
@@ -334,14 +373,14 @@ __attribute__((amdgpu_waves_per_eu(Fft2<T, P, E>::NT >= 512 ? 4 : 1))) void k_te
     const rsrc_t rpp = mkbuf(d.psip, tabn);
     const int mu = task - 7;
     const unsigned fm = 2 * mu * K::FSZ;
-    const rsrc_t rg = mkbuf(d.gspec + ((size_t)cell * 11 + 7 + mu) * 2 * K::FSZ, 2 * K::FSZ);
-    const rsrc_t rsp = mkbuf(d.terms + ((size_t)cell * kTermPlanes + task) * K::FSZ, K::FSZ);
+    const rsrc_t rg = mkbuf(d.gspec + (((size_t)cell * 11 + 7 + mu) * d.tg + grp) * 2 * K::FSZ, 2 * K::FSZ);
+    const rsrc_t rsp = mkbuf(d.terms + (size_t)blockIdx.x * K::FSZ, K::FSZ);
     const T e = mu == 0 ? wj : -wj;
     T Sacc[E];
 #pragma unroll
     for (int n = 0; n < E; ++n) Sacc[n] = 0;
 #pragma unroll 1
-    for (int j = 0; j < d.J; ++j) {
+    for (int j = j0; j < j1; ++j) {
       const unsigned tj = j * K::FSZ;
       T zr[E], zi[E];
 #pragma unroll
@@ -363,16 +402,25 @@ __attribute__((amdgpu_waves_per_eu(Fft2<T, P, E>::NT >= 512 ? 4 : 1))) void k_te
       }
       eng.template fwd2<true>(zr, zi);
 #pragma unroll
-      for (int k = 0; k < E; ++k) {
-        const unsigned o = k * K::NT;
-        const T a = bld<T>(rps, vo, (tj + o) * S), b = bld<T>(rpp, vo, (tj + o) * S);
-        T xr = a * zr[k] + b * zi[k], xi = b * zr[k] - a * zi[k];
-        if (j != 0) {
-          xr += bld<T>(rg, vo, o * S);
-          xi += bld<T>(rg, vo, (K::FSZ + o) * S);
+      for (int k0 = 0; k0 < E; k0 += TB) {
+        T a[TB], b[TB], gr[TB], gi[TB];
+#pragma unroll
+        for (int i = 0; i < TB; ++i) {
+          const unsigned o = (k0 + i) * K::NT;
+          a[i] = bld<T>(rps, vo, (tj + o) * S);
+          b[i] = bld<T>(rpp, vo, (tj + o) * S);
+          gr[i] = bld<T>(rg, vo, o * S);
+          gi[i] = bld<T>(rg, vo, (K::FSZ + o) * S);
         }
-        bst<T>(rg, xr, vo, o * S);
-        bst<T>(rg, xi, vo, (K::FSZ + o) * S);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < TB; ++i) {
+          const int k = k0 + i;
+          const unsigned o = k * K::NT;
+          bst<T>(rg, a[i] * zr[k] + b[i] * zi[k] + (j != j0 ? gr[i] : (T)0), vo, o * S);
+          bst<T>(rg, b[i] * zr[k] - a[i] * zi[k] + (j != j0 ? gi[i] : (T)0), vo, (K::FSZ + o) * S);
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
 #pragma unroll
@@ -381,8 +429,8 @@ __attribute__((amdgpu_waves_per_eu(Fft2<T, P, E>::NT >= 512 ? 4 : 1))) void k_te
 }
 
 // ------------------------------------------------------------------ I_3
-// Transpose of k_i3, one workgroup per (cell, j), Gauss-Legendre nodes in
-// symmetric pairs (m, m' = M-1-m; the middle node of an odd M alone).
+// Transpose of k_i3, one workgroup per (cell, j, group of d.gs node pairs;
+// k_grad_pre adds them), Gauss-Legendre nodes in symmetric pairs (m, m' = M-1-m; the middle node of an odd M alone).
 // With S the shift of node m, s_nu = S w_nu, b_bar the cotangent of the I_3
 // sums (b_bar_0 = -2 pi lam_0, b_bar_k = 2 pi lam_k), t_nu = S b_bar_nu,
 // Psi = inv2(psi'_j / P^2 fwd2(.)) (real, symmetric) and c = (pi/J) w_m,
@@ -410,18 +458,18 @@ __attribute__((amdgpu_waves_per_eu(Fft2<T, P, E>::NT >= 512 ? 4 : 1))) void k_te
 // tile allows (RREG), the rows' own fields s_a0, s_a1, t_a0, t_a1 are also
 // loaded into registers once per row pair instead of once per convolution.
 // The tuner picks WREG: the extra registers cost occupancy.
-// i3g[cell][j]: [0..3] w_bar (row real), [4..7] w_hat_bar packed as
+// i3g[task]: [0..3] w_bar (row real), [4..7] w_hat_bar packed as
 // (mu 0 + i mu 1), (mu 2 + i mu 3), re/im planes, col spec.
 template <typename T, int P, int E, bool WREG>
 __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_i3_vjp_reg(DevPlan<T> d, int ncells) {
   using K = Kern<T, P, E, I3Regs<T, P, E>::XB>;
   constexpr unsigned S = sizeof(T);
-  // elements between scheduling barriers in the element loops, which bound
-  // the loads in flight
-#ifndef QB_VJP_SG
-#define QB_VJP_SG 4
-#endif
-  constexpr int SG = QB_VJP_SG;
+  // elements whose loads are in flight together, all of them before the first
+  // store (see k_i3): as many as the registers hold.  48 cells at N = 32:
+  // float64 (E = 8) 19.7 -> 17.6 ms, float32 (E = 16) 12.3 -> 8.8; 16 cells at
+  // N = 64 in float32 48 -> 33; a batch of 4 spills in float64 at P = 128
+  // (66 against 50 ms).
+  constexpr int VB = P >= 128 && sizeof(T) == 8 ? 2 : 4, SG = 4;
   // registers: the transform operand, Y of the rows, w_bar of the rows
   // (WREG) and the rows' four shifted fields (RREG), E values each per
   // field and thread, beside about 48 for addresses and temporaries
@@ -441,10 +489,10 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_i3_vjp_reg(DevPlan<T> d
   typename K::Eng eng;
   setup(eng, smem, d.tw);
   const int task = xcd_task(blockIdx.x, gridDim.x);
-  const int cell = task / d.J;
-  const int j = task % d.J;
+  const int cell = task / (d.J * d.ng);
+  const int j = task / d.ng % d.J;
   const unsigned vo = threadIdx.x * S;
-  const size_t tb = (size_t)cell * d.J + j;
+  const size_t tb = (size_t)task;
   const rsrc_t rs = mkbuf(d.spec + (size_t)cell * 8 * K::FSZ, 8 * K::FSZ);
   const rsrc_t rw = mkbuf(d.wP + (size_t)cell * 5 * K::FSZ, 5 * K::FSZ);
   const rsrc_t rl = mkbuf(d.acot + ((size_t)cell * 16 + 8) * K::FSZ, 4 * K::FSZ);
@@ -472,17 +520,14 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_i3_vjp_reg(DevPlan<T> d
       const T a = bld<T>(rm, vo, (k * K::NT) * S);
       zr[k] *= a;
       zi[k] *= a;
+      if (k % 8 == 7) __builtin_amdgcn_sched_barrier(0);
     }
     eng.template inv2<true>(zr, zi);
   };
   auto ld = [&](rsrc_t r, int plane, unsigned o) { return bld<T>(r, vo, (plane * K::FSZ + o) * S); };
-  auto rmw = [&](rsrc_t r, int plane, unsigned o, T v) {
-    const unsigned off = (plane * K::FSZ + o) * S;
-    bst<T>(r, bld<T>(r, vo, off) + v, vo, off);
-  };
-  const int nnode = (d.M + 1) / 2;
+  const int mb = task % d.ng * d.gs, me = min((d.M + 1) / 2, mb + d.gs);
 #pragma unroll 1
-  for (int m = 0; m < nnode; ++m) {
+  for (int m = mb; m < me; ++m) {
     const bool paired = m != d.M - 1 - m;
     const T* px = d.phx + (((size_t)j * d.M + m) * P) * 2;
     const T* py = d.phy + (((size_t)j * d.M + m) * P) * 2 + 2 * E * eng.bq;
@@ -510,11 +555,9 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_i3_vjp_reg(DevPlan<T> d
           cmul(pxr, pxi, py[2 * k], py[2 * k + 1], er, ei);
           if (src == 0) {
             const unsigned fa = 2 * (2 * pr) * K::FSZ, fb = 2 * (2 * pr + 1) * K::FSZ;
-            T ar, ai, br, bi;
-            cmul(bld<T>(rs, vo, (fa + o) * S), bld<T>(rs, vo, (fa + K::FSZ + o) * S), er, ei, ar, ai);
-            cmul(bld<T>(rs, vo, (fb + o) * S), bld<T>(rs, vo, (fb + K::FSZ + o) * S), er, ei, br, bi);
-            zr[k] = ar - bi;
-            zi[k] = ai + br;
+            const T xr = bld<T>(rs, vo, (fa + o) * S) - bld<T>(rs, vo, (fb + K::FSZ + o) * S);
+            const T xi = bld<T>(rs, vo, (fa + K::FSZ + o) * S) + bld<T>(rs, vo, (fb + o) * S);
+            cmul(xr, xi, er, ei, zr[k], zi[k]);
           } else {
             cmul(ld(rh, 2 * pr, o), ld(rh, 2 * pr + 1, o), er, ei, zr[k], zi[k]);
           }
@@ -536,7 +579,7 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_i3_vjp_reg(DevPlan<T> d
 #pragma unroll 1
     for (int mp = 0; mp < 2; ++mp) {
       const int a0 = 2 * mp, a1 = 2 * mp + 1;
-      const bool first = m == 0 && mp == 0;
+      const bool first = m == mb && mp == 0;
       const T ea0 = a0 == 0 ? (T)1 : (T)-1;  // eta_a0; eta_a1 = -1
       T ya0[E], ya1[E], wa0[WREG ? E : 1], wa1[WREG ? E : 1];
 #pragma unroll
@@ -583,22 +626,36 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_i3_vjp_reg(DevPlan<T> d
         if constexpr (STG) fetch_lds_dw<T, K::NT, E>(rg, pfs, vo, nu * K::FSZ * S);
         conv(zr, zi);
         const unsigned pq = STG ? lds_fetch_wait() : 0u;
+        // batches of VB elements, all loads before the first store (as in k_i3)
 #pragma unroll
-        for (int n = 0; n < E; ++n) {
-          const unsigned o = n * K::NT;
-          const T b = ld(rl, nu, o), bb = c * b;
-          const T ta0v = row(ta0, rt, a0, n), ta1v = row(ta1, rt, a1, n);
-          ya0[n] += ea0 * bb * zr[n];
-          ya1[n] -= bb * zi[n];
-          const T gv = enu * c * (ta0v * zr[n] + ta1v * zi[n]);
-          {
-            const T gp = STG ? lds_elem<T, K::NT, E>(pfs, n, pq) : bld<T>(rg, vo, (nu * K::FSZ + o) * S);
-            bst<T>(rg, gv + (WREG && first ? (T)0 : gp), vo, (nu * K::FSZ + o) * S);
+        for (int n0 = 0; n0 < E; n0 += VB) {
+          T bv[VB], wv[VB], gp[VB], t0[VB], t1[VB], s0[VB], s1[VB];
+#pragma unroll
+          for (int i = 0; i < VB; ++i) {
+            const int n = n0 + i;
+            const unsigned o = n * K::NT;
+            bv[i] = ld(rl, nu, o);
+            wv[i] = ld(rw, nu, o);
+            gp[i] = STG ? lds_elem<T, K::NT, E>(pfs, n, pq) : ld(rg, nu, o);
+            t0[i] = row(ta0, rt, a0, n);
+            t1[i] = row(ta1, rt, a1, n);
+            s0[i] = row(sa0, rb, a0, n);
+            s1[i] = row(sa1, rb, a1, n);
           }
-          const T wv = enu * ld(rw, nu, o);
-          zr[n] = ea0 * b * row(sa0, rb, a0, n) + wv * ta0v;
-          zi[n] = wv * ta1v - b * row(sa1, rb, a1, n);
-          if (n % SG == SG - 1) __builtin_amdgcn_sched_barrier(0);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int i = 0; i < VB; ++i) {
+            const int n = n0 + i;
+            const T b = bv[i], bb = c * b;
+            ya0[n] += ea0 * bb * zr[n];
+            ya1[n] -= bb * zi[n];
+            const T gv = enu * c * (t0[i] * zr[n] + t1[i] * zi[n]);
+            bst<T>(rg, gv + (WREG && first ? (T)0 : gp[i]), vo, (nu * K::FSZ + n * K::NT) * S);
+            const T we = enu * wv[i];
+            zr[n] = ea0 * b * s0[i] + we * t0[i];
+            zi[n] = we * t1[i] - b * s1[i];
+          }
+          __builtin_amdgcn_sched_barrier(0);
         }
         if constexpr (STG) {
           fetch_lds_dw<T, K::NT, E>(rc, pfs, vo, nu * K::FSZ * S);
@@ -609,37 +666,56 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_i3_vjp_reg(DevPlan<T> d
         // next q input: s of the next nu (re-read on the last pass, unused)
         const int nx = nu < 3 ? nu + 1 : 3;
 #pragma unroll
-        for (int n = 0; n < E; ++n) {
-          const unsigned o = n * K::NT;
-          const T sv = c * (STG ? lds_elem<T, K::NT, E>(pfs + PFD, n, pr2) : ld(rb, nu, o));
-          if constexpr (WREG) {
-            wa0[WREG ? n : 0] += sv * zr[n];
-            wa1[WREG ? n : 0] += sv * zi[n];
-          } else {
-            rmw(rg, a0, o, sv * zr[n]);
-            rmw(rg, a1, o, sv * zi[n]);
+        for (int n0 = 0; n0 < E; n0 += VB) {
+          T sv[VB], w0[VB], w1[VB], yp[VB], sn[VB], g0[WREG ? 1 : VB], g1[WREG ? 1 : VB];
+#pragma unroll
+          for (int i = 0; i < VB; ++i) {
+            const int n = n0 + i;
+            const unsigned o = n * K::NT;
+            sv[i] = STG ? lds_elem<T, K::NT, E>(pfs + PFD, n, pr2) : ld(rb, nu, o);
+            w0[i] = ld(rw, a0, o);
+            w1[i] = ld(rw, a1, o);
+            // first row pair: the old value is read (in bounds) but dropped by
+            // a select, which keeps the loop free of branches
+            yp[i] = STG ? lds_elem<T, K::NT, E>(pfs, n, pr2) : ld(rc, nu, o);
+            sn[i] = ld(rb, nx, o);
+            if constexpr (!WREG) {
+              g0[WREG ? 0 : i] = ld(rg, a0, o);
+              g1[WREG ? 0 : i] = ld(rg, a1, o);
+            }
           }
-          const T w0 = ld(rw, a0, o), w1 = ld(rw, a1, o);
-          // first row pair: the old value is read (in bounds) but dropped by
-          // a select, which keeps the loop free of branches
-          const unsigned yo = (nu * K::FSZ + o) * S;
-          const T yp = STG ? lds_elem<T, K::NT, E>(pfs, n, pr2) : bld<T>(rc, vo, yo);
-          bst<T>(rc, c * (w0 * zr[n] + w1 * zi[n]) + (mp != 0 ? yp : (T)0), vo, yo);
-          const T sn = ld(rb, nx, o);
-          zr[n] = w0 * sn;
-          zi[n] = w1 * sn;
-          if (n % SG == SG - 1) __builtin_amdgcn_sched_barrier(0);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int i = 0; i < VB; ++i) {
+            const int n = n0 + i;
+            const unsigned o = n * K::NT;
+            const T sc = c * sv[i];
+            if constexpr (WREG) {
+              wa0[WREG ? n : 0] += sc * zr[n];
+              wa1[WREG ? n : 0] += sc * zi[n];
+            } else {
+              bst<T>(rg, g0[WREG ? 0 : i] + sc * zr[n], vo, (a0 * K::FSZ + o) * S);
+              bst<T>(rg, g1[WREG ? 0 : i] + sc * zi[n], vo, (a1 * K::FSZ + o) * S);
+            }
+            bst<T>(rc, c * (w0[i] * zr[n] + w1[i] * zi[n]) + (mp != 0 ? yp[i] : (T)0), vo, (nu * K::FSZ + o) * S);
+            zr[n] = w0[i] * sn[i];
+            zi[n] = w1[i] * sn[i];
+          }
+          __builtin_amdgcn_sched_barrier(0);
         }
       }
+      auto add = [&](rsrc_t r, int plane, const T* v) {
+        T old[E];
 #pragma unroll
-      for (int n = 0; n < E; ++n) {
-        const unsigned o = n * K::NT;
-        rmw(rc, a0, o, ya0[n]);
-        rmw(rc, a1, o, ya1[n]);
-        if constexpr (WREG) {
-          rmw(rg, a0, o, wa0[WREG ? n : 0]);
-          rmw(rg, a1, o, wa1[WREG ? n : 0]);
-        }
+        for (int n = 0; n < E; ++n) old[n] = ld(r, plane, n * K::NT);
+#pragma unroll
+        for (int n = 0; n < E; ++n) bst<T>(r, old[n] + v[n], vo, (plane * K::FSZ + n * K::NT) * S);
+      };
+      add(rc, a0, ya0);
+      add(rc, a1, ya1);
+      if constexpr (WREG) {
+        add(rg, a0, wa0);
+        add(rg, a1, wa1);
       }
     }
     // w_hat_bar += phase conj(F)(Y), packed pairs (0, 1), (2, 3).  Only its
@@ -658,19 +734,32 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_i3_vjp_reg(DevPlan<T> d
         zi[n] = -ld(rc, 2 * pr + 1, o);
       }
       eng.fwd2(zr, zi);
-#pragma unroll
-      for (int k = 0; k < E; ++k) {
-        const unsigned o = k * K::NT;
+      auto xi_off = [&](int k) {
         const int by = centered<P>(eng.bk(k));
-        const unsigned vk = (kx_in && by > -P / 4 && by < P / 4) ? vo : 0x80000000u;
-        T er, ei;
-        cmul(pxr, pxi, py[2 * k], py[2 * k + 1], er, ei);
-        T xr, xi;
-        cmul(zr[k], -zi[k], er, ei, xr, xi);
-        const unsigned fr = ((4 + 2 * pr) * K::FSZ + o) * S, fi = ((5 + 2 * pr) * K::FSZ + o) * S;
-        const T g0 = bld<T>(rg, vk, fr), g1 = bld<T>(rg, vk, fi);
-        bst<T>(rg, xr + (m != 0 ? g0 : (T)0), vk, fr);
-        bst<T>(rg, xi + (m != 0 ? g1 : (T)0), vk, fi);
+        return (kx_in && by > -P / 4 && by < P / 4) ? vo : 0x80000000u;
+      };
+#pragma unroll
+      for (int k0 = 0; k0 < E; k0 += VB) {
+        T g0[VB], g1[VB];
+#pragma unroll
+        for (int i = 0; i < VB; ++i) {
+          const unsigned o = (k0 + i) * K::NT, vk = xi_off(k0 + i);
+          g0[i] = bld<T>(rg, vk, ((4 + 2 * pr) * K::FSZ + o) * S);
+          g1[i] = bld<T>(rg, vk, ((5 + 2 * pr) * K::FSZ + o) * S);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < VB; ++i) {
+          const int k = k0 + i;
+          const unsigned o = k * K::NT, vk = xi_off(k);
+          T er, ei;
+          cmul(pxr, pxi, py[2 * k], py[2 * k + 1], er, ei);
+          T xr, xi;
+          cmul(zr[k], -zi[k], er, ei, xr, xi);
+          bst<T>(rg, xr + (m != mb ? g0[i] : (T)0), vk, ((4 + 2 * pr) * K::FSZ + o) * S);
+          bst<T>(rg, xi + (m != mb ? g1[i] : (T)0), vk, ((5 + 2 * pr) * K::FSZ + o) * S);
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
   }
@@ -680,10 +769,10 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_i3_vjp_reg(DevPlan<T> d
 // Elementwise gathering of every cotangent of the interpolants and of
 // w_hat into gsum[cell][8] (flat index e, the same in both layouts):
 //   q = 0..3  total real-space cotangent of w_mu on the P grid (row real):
-//             the I_3 partials summed over j, the assembly's explicit part,
+//             the I_3 partials summed over tasks, the assembly's explicit part,
 //             and 2 f0_bar for mu = 0
 //   q = 4..7  w_hat cotangents packed as (mu 0 + i mu 1), (mu 2 + i mu 3),
-//             re / im planes (col spec): the I_3 partials summed over j and
+//             re / im planes (col spec): the I_3 partials summed over tasks and
 //             the single-component spectra of the I_1, I_4 and I_2 tasks.
 template <typename T>
 __global__ void k_grad_pre(DevPlan<T> d, int ncells, int fsz) {
@@ -693,14 +782,16 @@ __global__ void k_grad_pre(DevPlan<T> d, int ncells, int fsz) {
   const size_t cell = idx / per, r = idx % per;
   const int q = (int)(r / fsz);
   const size_t e = r % fsz;
-  const T* src = d.i3g + cell * d.J * per + r;
+  const int ntask = d.J * d.ng;
+  const T* src = d.i3g + cell * ntask * per + r;
   T a = 0;
-  for (int j = 0; j < d.J; ++j) a += src[(size_t)j * per];
+#pragma unroll 8
+  for (int j = 0; j < ntask; ++j) a += src[(size_t)j * per];
   if (q < 4) {
     a += d.acot[(cell * 16 + 12 + q) * fsz + e];
     if (q == 0) {
       T f = 0;
-      for (int t = 0; t < 7; ++t) f += d.gf0[(cell * 7 + t) * fsz + e];
+      for (int t = 0; t < 7 * d.tg; ++t) f += d.gf0[(cell * 7 * d.tg + t) * fsz + e];
       a += (T)2 * f;
     }
   } else {
@@ -708,20 +799,23 @@ __global__ void k_grad_pre(DevPlan<T> d, int ncells, int fsz) {
     const int ma = 2 * pr, mb = 2 * pr + 1;
     // task slots of gspec: I_1 (mu >= 1) at mu - 1, I_4 at 3 + mu, I_2 at 7 + mu
     // k_terms_vjp leaves H with the cotangent (H(k) + conj H(-k)) / 2
-    const T* gs = d.gspec + cell * 22 * fsz + e;
+    const T* gs = d.gspec + cell * 22 * d.tg * fsz + e;
     const unsigned ne = d.negk[e];
-    const T* gn = d.gspec + cell * 22 * fsz + (ne & 0x7fffffffu);
+    const T* gn = d.gspec + cell * 22 * d.tg * fsz + (ne & 0x7fffffffu);
     const T sn = (ne >> 31) ? (T)-1 : (T)1;  // the kept spectra's signs at -k and k differ
     T ar = 0, ai = 0, br = 0, bi = 0;
     const int sa[3] = {ma - 1, 3 + ma, 7 + ma}, sb[3] = {mb - 1, 3 + mb, 7 + mb};
-    for (int t = 0; t < 3; ++t) {
-      if (sa[t] >= 0) {
-        ar += gs[(size_t)(2 * sa[t]) * fsz] + sn * gn[(size_t)(2 * sa[t]) * fsz];
-        ai += gs[(size_t)(2 * sa[t] + 1) * fsz] - sn * gn[(size_t)(2 * sa[t] + 1) * fsz];
+    for (int t = 0; t < 3; ++t)
+      for (int g = 0; g < d.tg; ++g) {
+        if (sa[t] >= 0) {
+          const size_t o = (size_t)2 * (sa[t] * d.tg + g) * fsz;
+          ar += gs[o] + sn * gn[o];
+          ai += gs[o + fsz] - sn * gn[o + fsz];
+        }
+        const size_t o = (size_t)2 * (sb[t] * d.tg + g) * fsz;
+        br += gs[o] + sn * gn[o];
+        bi += gs[o + fsz] - sn * gn[o + fsz];
       }
-      br += gs[(size_t)(2 * sb[t]) * fsz] + sn * gn[(size_t)(2 * sb[t]) * fsz];
-      bi += gs[(size_t)(2 * sb[t] + 1) * fsz] - sn * gn[(size_t)(2 * sb[t] + 1) * fsz];
-    }
     a += (T)0.5 * (im == 0 ? ar - bi : ai + br);
   }
   d.gsum[cell * per + r] = a;
@@ -739,7 +833,7 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_grad_out(DevPlan<T> d, 
   __shared__ T smem[K::LDS];
   typename K::Eng eng;
   setup(eng, smem, d.tw);
-  const int lc = blockIdx.x;
+  const int lc = blockIdx.x >> 1, pr = blockIdx.x & 1;
   const int cell = cell0 + lc;
   const int N = P / 2;
   const unsigned vo = threadIdx.x * S;
@@ -748,8 +842,7 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_grad_out(DevPlan<T> d, 
   const int bx = centered<P>(eng.line);
   const bool kx_in = bx > -N / 2 && bx < N / 2;
   const T sc = (T)1 / (T)(N * N);
-#pragma unroll 1
-  for (int pr = 0; pr < 2; ++pr) {
+  {
     const int ma = 2 * pr, mb = 2 * pr + 1;
     T zr[E], zi[E];
 #pragma unroll

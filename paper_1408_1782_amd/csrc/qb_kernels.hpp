@@ -53,7 +53,7 @@ struct DevPlan {
   T* spec;   // [cells][4][2][P*P]  w_hat_mu, col spec
   T* wP;     // [cells][5][P*P]     w_mu and f0 = 2 w0 - 1 on the P grid, row real
   T* terms;  // [cells][11][tg][P*P]  I_1 (3), I_4 (4), I_2 (one per Pauli component) real-space fields,
-             //                     one per group of directions (k_terms_vjp: tg = 1)
+             //                     one per group of directions
   T* acc;    // [cells][7][tg][2][P*P]  spectral accumulators of the I_1 / I_4 tasks
   // I_3, per task (cell, j, node group)
   T* i3s;    // [tasks][4 or 6][P*P]  shifted fields of the current (j, m) (+ partner sums)
@@ -66,15 +66,15 @@ struct DevPlan {
   // adjoint work buffers (present once the plan's adjoint is enabled)
   T* lamP;   // [cells][4][P*P]     cotangent of the assembled fields, row real
   T* acot;   // [cells][16][P*P]    assembly cotangents: g (3), y (4), S (1), b (4), w direct (4)
-  T* gspec;  // [cells][11][2][P*P] cotangents of w_hat from I_1 (3), I_4 (4), I_2 (4), col spec
-  T* gf0;    // [cells][7][P*P]     f0 cotangents of the I_1 / I_4 tasks, row real
-  T* i3g;    // [cells][J][8][P*P]  I_3 adjoint per (cell, j): w cotangent (4, row real),
+  T* gspec;  // [cells][11][tg][2][P*P] cotangents of w_hat from I_1 (3), I_4 (4), I_2 (4), col spec
+  T* gf0;    // [cells][7][tg][P*P] f0 cotangents of the I_1 / I_4 tasks, row real
+  T* i3g;    // [tasks][8][P*P]     I_3 adjoint per task: w cotangent (4, row real),
              //                     packed w_hat cotangents (2 pairs x re/im, col spec)
-  T* i3sb;   // [cells][J][4][P*P]  cotangent of the shifted fields of the current (j, m)
-  T* i3t;    // [cells][J][4][P*P]  shifted cotangents of the I_3 sums for the current (j, m)
+  T* i3sb;   // [tasks][4][P*P]      cotangent of the shifted fields of the current (j, m)
+  T* i3t;    // [tasks][4][P*P]      shifted cotangents of the I_3 sums for the current (j, m)
   T* lamh;   // [cells][4][P*P]     spectrum of lamP, packed pairs, col spec
   T* gsum;   // [cells][8][P*P]     gathered cotangents (k_grad_pre)
-  T* fwa;    // [cells][7][2][P*P]  spectral accumulators of the forward I_1 / I_4 fields in k_terms_vjp
+  T* fwa;    // [cells][7][tg][2][P*P]  spectral accumulators of the forward I_1 / I_4 fields in k_terms_vjp
 };
 
 // ------------------------------------------------------------------ helpers
@@ -558,14 +558,15 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) __attribute__((amdgpu_waves_pe
   // Elements whose loads are in flight together, in the loops that form the
   // shifted fields and the products (SG), multiply by psi' (SM), use up a
   // convolution (SB) and accumulate the partner spectra (PB): as many as the
-  // registers beside the transform operand hold.  In float32 at P = 128 with
-  // SB = 4 and no row registers 60.5 ms over 64 cells (N = 64), 65.8 with the
-  // rows in registers and 37 spilled, 74.4 one element at a time; one step
-  // more of any of them spills (SB = 8: 62 to 63).
+  // registers beside the transform operand hold, with a scheduling barrier
+  // between a batch's loads and its arithmetic (without it the compiler moves
+  // loads up until registers spill).  64 cells at N = 64 in float32: one
+  // element at a time 74.4 ms, as here 56.8, with SB = 8 58.5, with the rows'
+  // shifted fields in registers too (37 spilled) 65.8.
   constexpr int SG = P >= 128 ? 4 : 8;
-  constexpr int SM = PMEM ? 4 : 8;
+  constexpr int SM = PMEM ? 2 : 8;
   constexpr int SB = PMEM ? 2 : 4;
-  constexpr int PB = PMEM ? 1 : 8;
+  constexpr int PB = PMEM ? 1 : 4;
   const unsigned tid = threadIdx.x;
   typename K::Eng eng;
   setup(eng, smem, d.tw);
@@ -663,24 +664,40 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) __attribute__((amdgpu_waves_pe
         if constexpr (PF) fetch_lds<T, K::NT, E>(ro, pf, vo, nu * K::FSZ * S);
         T zr[E], zi[E];
 #pragma unroll
-        for (int n = 0; n < E; ++n) {
-          const unsigned o = n * K::NT;
-          T sv;
-          if constexpr (SREG)
-            sv = pick4(nu, s[0][n], s[SREG ? 1 : 0][n], s[SREG ? 2 : 0][n], s[SREG ? 3 : 0][n]);
-          else
-            sv = bld<T>(rb, vo, (nu * K::FSZ + o) * S);
-          zr[n] = bld<T>(rw, vo, (m0 * K::FSZ + o) * S) * sv;
-          zi[n] = bld<T>(rw, vo, (m1 * K::FSZ + o) * S) * sv;
-          if (n % SG == SG - 1) __builtin_amdgcn_sched_barrier(0);
+        for (int b = 0; b < E; b += SG) {
+          T sv[SG];
+#pragma unroll
+          for (int i = 0; i < SG; ++i) {
+            const int n = b + i;
+            const unsigned o = n * K::NT;
+            if constexpr (SREG)
+              sv[i] = pick4(nu, s[0][n], s[SREG ? 1 : 0][n], s[SREG ? 2 : 0][n], s[SREG ? 3 : 0][n]);
+            else
+              sv[i] = bld<T>(rb, vo, (nu * K::FSZ + o) * S);
+            zr[n] = bld<T>(rw, vo, (m0 * K::FSZ + o) * S);
+            zi[n] = bld<T>(rw, vo, (m1 * K::FSZ + o) * S);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int i = 0; i < SG; ++i) {
+            zr[b + i] *= sv[i];
+            zi[b + i] *= sv[i];
+          }
+          __builtin_amdgcn_sched_barrier(0);
         }
         eng.template fwd2<true>(zr, zi);
 #pragma unroll
-        for (int k = 0; k < E; ++k) {
-          const T a = bld<T>(rm, vo, (k * K::NT) * S);
-          zr[k] *= a;
-          zi[k] *= a;
-          if (k % SM == SM - 1) __builtin_amdgcn_sched_barrier(0);
+        for (int b = 0; b < E; b += SM) {
+          T a[SM];
+#pragma unroll
+          for (int i = 0; i < SM; ++i) a[i] = bld<T>(rm, vo, ((b + i) * K::NT) * S);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int i = 0; i < SM; ++i) {
+            zr[b + i] *= a[i];
+            zi[b + i] *= a[i];
+          }
+          __builtin_amdgcn_sched_barrier(0);
         }
         eng.template inv2<true>(zr, zi);
         const T e0 = m0 == 0 ? wgt : -wgt;
@@ -776,6 +793,7 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) __attribute__((amdgpu_waves_pe
             pr0[i] = bld<T>(rp, vk, (fr + o) * S);
             pi0[i] = bld<T>(rp, vk, (fi + o) * S);
           }
+          __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int i = 0; i < PB; ++i) {
             const int k = b + i;

@@ -410,13 +410,10 @@ template <typename T>
 bool carve_collision(Arena& a, const qb_plan_s* pl, size_t C, size_t I, bool one, CollBufs& b) {
   const size_t FSZ = (size_t)pl->P * pl->P, J = pl->prob.J, t = sizeof(T);
   const size_t ng = one ? 1 : max_node_groups(pl->prob), tg = term_groups(pl->prob.J, one);
-  // the spectral accumulators of k_terms are in memory for some float64 tiles
-  // only; k_terms_vjp keeps one set per cell there
-  const size_t ta = sizeof(T) == 8 && pl->P >= 64 ? tg : 1;
   const size_t tasks = I * J * ng;
   return a.take(&b.i3s, tasks * qb::kI3sPlanes<T> * FSZ * t) && a.take(&b.spec, C * 8 * FSZ * t) &&
          a.take(&b.wP, C * 5 * FSZ * t) && a.take(&b.terms, C * qb::kTermPlanes * tg * FSZ * t) &&
-         a.take(&b.acc, C * 14 * ta * FSZ * t) && a.take(&b.i3o, tasks * 4 * FSZ * t) &&
+         a.take(&b.acc, C * 14 * tg * FSZ * t) && a.take(&b.i3o, tasks * 4 * FSZ * t) &&
          a.take(&b.i3sum, C * 4 * FSZ * t) && a.take(&b.i3p, tasks * 4 * FSZ * t) && a.take(&b.i3ps, C * 4 * FSZ * t);
 }
 
@@ -453,11 +450,12 @@ bool build_adjoint(qb_plan_s* pl) {
   void** states[] = {&pl->wn, &pl->wa, &pl->w1, &pl->wb, &pl->lb, &pl->ls, &pl->la, &pl->cg, &pl->g0};
   for (void** q : states)
     if (!pl->alloc_adj(q, st)) return false;
+  const size_t tg = term_groups(p.J, false), tasks = (size_t)pl->i3cells * J * max_node_groups(p);
   return pl->alloc_adj(&pl->lamP, C * 4 * FSZ * b) && pl->alloc_adj(&pl->acot, C * 16 * FSZ * b) &&
-         pl->alloc_adj(&pl->gspec, C * 22 * FSZ * b) && pl->alloc_adj(&pl->gf0, C * 7 * FSZ * b) &&
-         pl->alloc_adj(&pl->i3g, C * J * 8 * FSZ * b) && pl->alloc_adj(&pl->i3sb, C * J * 4 * FSZ * b) &&
-         pl->alloc_adj(&pl->gsum, C * 8 * FSZ * b) && pl->alloc_adj(&pl->i3t, C * J * 4 * FSZ * b) &&
-         pl->alloc_adj(&pl->lamh, C * 4 * FSZ * b) && pl->alloc_adj(&pl->fwa, C * 14 * FSZ * b) &&
+         pl->alloc_adj(&pl->gspec, C * 22 * tg * FSZ * b) && pl->alloc_adj(&pl->gf0, C * 7 * tg * FSZ * b) &&
+         pl->alloc_adj(&pl->i3g, tasks * 8 * FSZ * b) && pl->alloc_adj(&pl->i3sb, tasks * 4 * FSZ * b) &&
+         pl->alloc_adj(&pl->gsum, C * 8 * FSZ * b) && pl->alloc_adj(&pl->i3t, tasks * 4 * FSZ * b) &&
+         pl->alloc_adj(&pl->lamh, C * 4 * FSZ * b) && pl->alloc_adj(&pl->fwa, C * 14 * tg * FSZ * b) &&
          pl->alloc_adj(&pl->ext, (size_t)4 * (p.Nx + 4) * p.N * p.N * b) &&
          pl->alloc_adj((void**)&pl->lflux, 2 * sizeof(double));
 }

@@ -55,26 +55,36 @@ bool collision_vjp_pipeline(qb_plan_s* pl, const T* w, const T* lam, T* out, int
                             hipStream_t s) {
   constexpr int NT = qb::Fft2<T, P, E>::NT;
   DevPlan<T> d = devplan<T>(pl, pl->vjp_tab);
+  node_groups((d.M + 1) / 2, false, d.gs, d.ng);  // the reverse kernel always pairs its nodes
   int id = pl->begin(QB_K_DFT_IN, s);
   hipLaunchKernelGGL((qb::k_dft_in<T, P, E>), dim3(4 * ncells), dim3(NT), 0, s, d, w, cell0);
   pl->end(id, s);
   // the forward I_1 / I_4 / I_2 fields are formed inside k_terms_vjp
   id = pl->begin(QB_K_ADJOINT, s);
-  hipLaunchKernelGGL((qb::k_lam_in<T, P, E>), dim3(ncells), dim3(NT), 0, s, d, lam, cell0);
+  hipLaunchKernelGGL((qb::k_lam_in<T, P, E>), dim3(2 * ncells), dim3(NT), 0, s, d, lam, cell0);
   const size_t nel = (size_t)ncells * P * P;
   hipLaunchKernelGGL((qb::k_assemble_vjp<T>), dim3(blocks(nel, 256)), dim3(256), 0, s, d, ncells, P * P, 0);
-  hipLaunchKernelGGL((qb::k_terms_vjp<T, P, E>), dim3(ncells * qb::kTermsVjpTasks), dim3(NT), 0, s, d);
+  hipLaunchKernelGGL((qb::k_terms_vjp<T, P, E>), dim3(ncells * qb::kTermsVjpTasks * d.tg), dim3(NT), 0, s, d);
   hipLaunchKernelGGL((qb::k_assemble_vjp<T>), dim3(blocks(nel, 256)), dim3(256), 0, s, d, ncells, P * P, 1);
   pl->end(id, s);
-  id = pl->begin(QB_K_I3_ADJOINT, s);
-  if (pl->vjp_variant == 1)
-    hipLaunchKernelGGL((qb::k_i3_vjp_reg<T, P, E, true>), dim3(ncells * d.J), dim3(NT), 0, s, d, ncells);
-  else
-    hipLaunchKernelGGL((qb::k_i3_vjp_reg<T, P, E, false>), dim3(ncells * d.J), dim3(NT), 0, s, d, ncells);
-  pl->end(id, s);
+  for (int c0 = 0; c0 < ncells; c0 += pl->i3cells) {
+    const int nc = std::min(pl->i3cells, ncells - c0);
+    const size_t F = (size_t)c0 * P * P;
+    DevPlan<T> dc = d;
+    dc.spec += 8 * F, dc.wP += 5 * F, dc.acot += 16 * F, dc.lamh += 4 * F, dc.gsum += 8 * F;
+    dc.gf0 += 7 * d.tg * F, dc.gspec += 22 * d.tg * F;
+    id = pl->begin(QB_K_I3_ADJOINT, s);
+    if (pl->vjp_variant == 1)
+      hipLaunchKernelGGL((qb::k_i3_vjp_reg<T, P, E, true>), dim3(nc * d.J * d.ng), dim3(NT), 0, s, dc, nc);
+    else
+      hipLaunchKernelGGL((qb::k_i3_vjp_reg<T, P, E, false>), dim3(nc * d.J * d.ng), dim3(NT), 0, s, dc, nc);
+    pl->end(id, s);
+    id = pl->begin(QB_K_ADJOINT, s);
+    hipLaunchKernelGGL((qb::k_grad_pre<T>), dim3(blocks((size_t)nc * P * P * 8, 256)), dim3(256), 0, s, dc, nc, P * P);
+    pl->end(id, s);
+  }
   id = pl->begin(QB_K_ADJOINT, s);
-  hipLaunchKernelGGL((qb::k_grad_pre<T>), dim3(blocks(nel * 8, 256)), dim3(256), 0, s, d, ncells, P * P);
-  hipLaunchKernelGGL((qb::k_grad_out<T, P, E>), dim3(ncells), dim3(NT), 0, s, d, out, cell0);
+  hipLaunchKernelGGL((qb::k_grad_out<T, P, E>), dim3(2 * ncells), dim3(NT), 0, s, d, out, cell0);
   pl->end(id, s);
   return hip_ok(hipGetLastError(), "collision adjoint launch");
 }
