@@ -275,8 +275,9 @@ qb_status qb_diagnostics(qb_plan plan, const void* W, const void* C, const qb_fd
 /* ---------------------------------------------------------------------------
  * FFT tile shapes.  Every padded-grid transform runs in one workgroup that
  * holds the P x P field in registers, E elements per thread and P / E
- * threads per line.  Compiled shapes: P = 32: E = 16 (default), 8;
- * P = 64: E = 16 (default), 32, 8; P = 128: E = 16 (default), 32.
+ * threads per line.  Compiled shapes: P = 32: E = 16, 8; P = 64: E = 16,
+ * 32, 8; P = 128: E = 16, 32.  A plan starts with the shape measured fastest:
+ * 16, and 8 at P = 32 in float64.
  * ------------------------------------------------------------------------- */
 
 /* Use tile shape E on this plan (QB_ENOTSUP if not compiled for its P).
@@ -302,8 +303,9 @@ qb_status qb_plan_set_pairing(qb_plan plan, int32_t paired);
 
 /* Tile shape E of the reverse-mode pipeline (qb_collision_vjp and the
  * collision adjoints of qb_adjoint_step), independent of the forward tile;
- * 0 follows the forward tile (the default).  QB_ENOTSUP if E is not
- * compiled for the plan's padded grid.  Synchronous the first time a shape
+ * 0 follows the forward tile.  A plan starts with the shape measured fastest
+ * (8 at P = 32 and 64 in float64, else 16).  QB_ENOTSUP if E is not compiled
+ * for the plan's padded grid.  Synchronous the first time a shape
  * is used (fills its tables). */
 qb_status qb_plan_set_adjoint_tile(qb_plan plan, int32_t E);
 

@@ -93,7 +93,7 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_lam_in(DevPlan<T> d, co
       zr[n] = on_grid ? la[i * N] : (T)0;
       zi[n] = on_grid ? lb[i * N] : (T)0;
     }
-    eng.template fwd2<true>(zr, zi);
+    eng.template fwd2<true, !grouped<T>>(zr, zi);
 #pragma unroll
     for (int k = 0; k < E; ++k) {
       const int by = centered<P>(eng.bk(k));
@@ -104,7 +104,7 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_lam_in(DevPlan<T> d, co
       bst<T>(rh, zr[k], vo, ((2 * pr) * K::FSZ + k * K::NT) * S);
       bst<T>(rh, zi[k], vo, ((2 * pr + 1) * K::FSZ + k * K::NT) * S);
     }
-    eng.template inv2<true>(zr, zi);
+    eng.template inv2<true, !grouped<T>>(zr, zi);
 #pragma unroll
     for (int n = 0; n < E; ++n) {
       bst<T>(ro, zr[n], vo, ((2 * pr) * K::FSZ + n * K::NT) * S);
@@ -259,7 +259,7 @@ __attribute__((amdgpu_waves_per_eu(Fft2<T, P, E>::NT >= 512 ? 4 : 1))) void k_te
         zr[k] = cr * dr - ci * di;
         zi[k] = cr * di + ci * dr;
       }
-      eng.template inv2<true>(zr, zi);
+      eng.template inv2<true, true>(zr, zi);
 #pragma unroll
       for (int n = 0; n < E; ++n) {
         Br[n] = zr[n];
@@ -275,7 +275,7 @@ __attribute__((amdgpu_waves_per_eu(Fft2<T, P, E>::NT >= 512 ? 4 : 1))) void k_te
         zr[k] = sr * cr - si * ci;
         zi[k] = sr * ci + si * cr;
       }
-      eng.inv2(zr, zi);
+      eng.template inv2<true>(zr, zi);
       // batches of TB elements, all loads before the first store (see k_i3;
       // without the scheduling barrier between them up to 200 registers
       // spill); a value not yet written is read too and dropped by a select
@@ -301,7 +301,7 @@ __attribute__((amdgpu_waves_per_eu(Fft2<T, P, E>::NT >= 512 ? 4 : 1))) void k_te
         __builtin_amdgcn_sched_barrier(0);
       }
       // the pair's forward contribution cout fwd2(f0 A)
-      eng.template fwd2<true>(zr, zi);
+      eng.template fwd2<true, true>(zr, zi);
 #pragma unroll
       for (int k0 = 0; k0 < E; k0 += TB) {
         T o1[TB], o2[TB], pr[TB], pi[TB];
@@ -332,7 +332,7 @@ __attribute__((amdgpu_waves_per_eu(Fft2<T, P, E>::NT >= 512 ? 4 : 1))) void k_te
         zr[n] = f0 * Br[n];
         zi[n] = f0 * Bi[n];
       }
-      eng.fwd2(zr, zi);
+      eng.template fwd2<true>(zr, zi);
 #pragma unroll
       for (int k0 = 0; k0 < E; k0 += TB) {
         T i1[TB], i2[TB], gr[TB], gi[TB];
@@ -555,14 +555,13 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_i3_vjp_reg(DevPlan<T> d
           cmul(pxr, pxi, py[2 * k], py[2 * k + 1], er, ei);
           if (src == 0) {
             const unsigned fa = 2 * (2 * pr) * K::FSZ, fb = 2 * (2 * pr + 1) * K::FSZ;
-            const T xr = bld<T>(rs, vo, (fa + o) * S) - bld<T>(rs, vo, (fb + K::FSZ + o) * S);
-            const T xi = bld<T>(rs, vo, (fa + K::FSZ + o) * S) + bld<T>(rs, vo, (fb + o) * S);
-            cmul(xr, xi, er, ei, zr[k], zi[k]);
+            shift_pair(bld<T>(rs, vo, (fa + o) * S), bld<T>(rs, vo, (fa + K::FSZ + o) * S),
+                       bld<T>(rs, vo, (fb + o) * S), bld<T>(rs, vo, (fb + K::FSZ + o) * S), er, ei, zr[k], zi[k]);
           } else {
             cmul(ld(rh, 2 * pr, o), ld(rh, 2 * pr + 1, o), er, ei, zr[k], zi[k]);
           }
         }
-        eng.inv2(zr, zi);
+        eng.template inv2<!grouped<T>, !grouped<T>>(zr, zi);
         // t carries the B-term factors of b_bar: -2 pi (mu = 0), 2 pi (mu > 0)
         const T fa = src == 0 ? (T)1 : (T)(pr == 0 ? -2.0 * kPi : 2.0 * kPi);
         const T fb = src == 0 ? (T)1 : (T)(2.0 * kPi);
@@ -733,33 +732,50 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_i3_vjp_reg(DevPlan<T> d
         zr[n] = ld(rc, 2 * pr, o);
         zi[n] = -ld(rc, 2 * pr + 1, o);
       }
-      eng.fwd2(zr, zi);
+      eng.template fwd2<!grouped<T>, !grouped<T>>(zr, zi);
       auto xi_off = [&](int k) {
         const int by = centered<P>(eng.bk(k));
         return (kx_in && by > -P / 4 && by < P / 4) ? vo : 0x80000000u;
       };
+      if constexpr (grouped<T>) {
 #pragma unroll
-      for (int k0 = 0; k0 < E; k0 += VB) {
-        T g0[VB], g1[VB];
+        for (int k0 = 0; k0 < E; k0 += VB) {
+          T g0[VB], g1[VB];
 #pragma unroll
-        for (int i = 0; i < VB; ++i) {
-          const unsigned o = (k0 + i) * K::NT, vk = xi_off(k0 + i);
-          g0[i] = bld<T>(rg, vk, ((4 + 2 * pr) * K::FSZ + o) * S);
-          g1[i] = bld<T>(rg, vk, ((5 + 2 * pr) * K::FSZ + o) * S);
+          for (int i = 0; i < VB; ++i) {
+            const unsigned o = (k0 + i) * K::NT, vk = xi_off(k0 + i);
+            g0[i] = bld<T>(rg, vk, ((4 + 2 * pr) * K::FSZ + o) * S);
+            g1[i] = bld<T>(rg, vk, ((5 + 2 * pr) * K::FSZ + o) * S);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int i = 0; i < VB; ++i) {
+            const int k = k0 + i;
+            const unsigned o = k * K::NT, vk = xi_off(k);
+            T er, ei;
+            cmul(pxr, pxi, py[2 * k], py[2 * k + 1], er, ei);
+            T xr, xi;
+            cmul(zr[k], -zi[k], er, ei, xr, xi);
+            bst<T>(rg, xr + (m != mb ? g0[i] : (T)0), vk, ((4 + 2 * pr) * K::FSZ + o) * S);
+            bst<T>(rg, xi + (m != mb ? g1[i] : (T)0), vk, ((5 + 2 * pr) * K::FSZ + o) * S);
+          }
+          __builtin_amdgcn_sched_barrier(0);
         }
-        __builtin_amdgcn_sched_barrier(0);
+      } else {
+        // (element by element: the order float32 rounds these sums in)
 #pragma unroll
-        for (int i = 0; i < VB; ++i) {
-          const int k = k0 + i;
-          const unsigned o = k * K::NT, vk = xi_off(k);
+        for (int k = 0; k < E; ++k) {
+          const unsigned o = k * K::NT;
+          const unsigned vk = xi_off(k);
           T er, ei;
           cmul(pxr, pxi, py[2 * k], py[2 * k + 1], er, ei);
           T xr, xi;
           cmul(zr[k], -zi[k], er, ei, xr, xi);
-          bst<T>(rg, xr + (m != mb ? g0[i] : (T)0), vk, ((4 + 2 * pr) * K::FSZ + o) * S);
-          bst<T>(rg, xi + (m != mb ? g1[i] : (T)0), vk, ((5 + 2 * pr) * K::FSZ + o) * S);
+          const unsigned fr = ((4 + 2 * pr) * K::FSZ + o) * S, fi = ((5 + 2 * pr) * K::FSZ + o) * S;
+          const T g0 = bld<T>(rg, vk, fr), g1 = bld<T>(rg, vk, fi);
+          bst<T>(rg, xr + (m != mb ? g0 : (T)0), vk, fr);
+          bst<T>(rg, xi + (m != mb ? g1 : (T)0), vk, fi);
         }
-        __builtin_amdgcn_sched_barrier(0);
       }
     }
   }
@@ -851,7 +867,7 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_grad_out(DevPlan<T> d, 
       zr[n] = bld<T>(r3, vo, (ma * K::FSZ + o) * S);
       zi[n] = -bld<T>(r3, vo, (mb * K::FSZ + o) * S);
     }
-    eng.template fwd2<true>(zr, zi);  // conj(F)(a + i b) = conj(fwd2(a - i b))
+    eng.template fwd2<true, !grouped<T>>(zr, zi);  // conj(F)(a + i b) = conj(fwd2(a - i b))
 #pragma unroll
     for (int k = 0; k < E; ++k) {
       const unsigned o = k * K::NT;
@@ -863,7 +879,7 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_grad_out(DevPlan<T> d, 
       zr[k] = in ? Zr * sc : (T)0;
       zi[k] = in ? -Zi * sc : (T)0;
     }
-    eng.template inv2<true>(zr, zi);
+    eng.template inv2<true, !grouped<T>>(zr, zi);
     const int y = eng.line;
     if (((eng.q | y) & 1) == 0) {
       T* ga = gout + ma * cs + (size_t)cell * N * N + (centered<P>(y) / 2 + N / 2);

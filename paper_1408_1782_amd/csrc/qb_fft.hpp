@@ -106,6 +106,13 @@ __host__ __device__ inline int bitrev_rt(int v, int bits) {
   return r;
 }
 
+template <typename T>
+__device__ __forceinline__ void cmul(T ar, T ai, T br, T bi, T& cr, T& ci) {
+  const T r = ar * br - ai * bi;
+  ci = ar * bi + ai * br;
+  cr = r;
+}
+
 // ------------------------------------------------------------------ in-register FFT
 // y[k] = sum_n x[O + S n] exp(DIR * 2 pi i n k / E), natural order in and out.
 template <typename T, int E, int DIR>
@@ -263,6 +270,9 @@ struct Fft2 {
   static_assert(E * TPR == P, "E * TPR must equal P");
   static_assert(P % BW == 0, "P must be a multiple of the bank width");
 
+  // whether the spectra carry the lane signs of lanes_fwd
+  static constexpr bool SIGNED = !(sizeof(T) == 4 && P == 128);
+
   int t, line, q, bq;
   T* lds;          // transpose buffer, LDS_SCALARS scalars
   const T* tw;     // LDS: (cos, sin)(2 pi q k / P) at [q][k], q < TPR, k < E, row stride TWS
@@ -340,7 +350,7 @@ struct Fft2 {
       add_lanes<7>(zr, sg);
       add_lanes<7>(zi, sg);
 #pragma unroll
-      for (int k = 0; k < E; ++k) cmul_by(zr[k], zi[k], wr, wi);
+      for (int k = 0; k < E; ++k) cmul(zr[k], zi[k], wr, wi, zr[k], zi[k]);
     }
     if constexpr (TPR >= 4) {
       const T sg = (q & 2) ? (T)-1 : (T)1;
@@ -385,15 +395,100 @@ struct Fft2 {
       T wr, wi;
       w8<+1>(wr, wi);
 #pragma unroll
-      for (int k = 0; k < E; ++k) cmul_by(zr[k], zi[k], wr, wi);
+      for (int k = 0; k < E; ++k) cmul(zr[k], zi[k], wr, wi, zr[k], zi[k]);
       add_lanes<7>(zr, sg);
       add_lanes<7>(zi, sg);
     }
   }
-  static __device__ __forceinline__ void cmul_by(T& r, T& i, T c, T s) {
-    const T x = r * c - i * s;
-    i = r * s + i * c;
-    r = x;
+
+  // twiddle w_8^r, r = 0..3, of the H = 4 lane stage (conjugated for the
+  // inverse), as (re, im)
+  template <int SG>
+  __device__ __forceinline__ void w8_true(int r, T& wr, T& wi) const {
+    const T c = (T)0.70710678118654752440;
+    wr = r == 0 ? (T)1 : (r == 1 ? c : (r == 2 ? (T)0 : -c));
+    const T s = r == 0 ? (T)0 : (r == 2 ? (T)1 : c);
+    wi = SG < 0 ? -s : s;
+  }
+
+  // The lane stages with the upper lanes' sign in the multiply-add (a move and
+  // an FMA per value) and no sign left on the spectrum.
+  // Cross-lane DFT of size TPR for every k.  Forward (decimation in
+  // frequency, natural lane order in, bit-reversed out):
+  //   stage H = TPR/2 .. 1: lower lane z + o, upper lane (o - z) w_{2H}^{q mod H}
+  // The H = 2 stage twiddle is w_4 = -i (lanes with q mod 4 = 3), applied as a
+  // component swap; the H = 4 stage (TPR = 8) multiplies the upper lanes by
+  // w_8^{q mod 4}.
+  __device__ __forceinline__ void lanes_fwd_true(T (&zr)[E], T (&zi)[E]) const {
+    if constexpr (TPR == 8) {
+      const T sg = (q & 4) ? (T)-1 : (T)1;
+      T wr, wi;
+      w8_true<-1>((q & 4) ? (q & 3) : 0, wr, wi);
+#pragma unroll
+      for (int k = 0; k < E; ++k) {
+        const T orr = xor_lane<7>(zr[k]), oi = xor_lane<7>(zi[k]);
+        const T dr = sg * zr[k] + orr, di = sg * zi[k] + oi;
+        zr[k] = dr * wr - di * wi;
+        zi[k] = dr * wi + di * wr;
+      }
+    }
+    if constexpr (TPR >= 4) {
+      const T sg = (q & 2) ? (T)-1 : (T)1;
+      const bool rot = (q & 3) == 3;
+#pragma unroll
+      for (int k = 0; k < E; ++k) {
+        const T orr = xor_lane<2>(zr[k]), oi = xor_lane<2>(zi[k]);
+        const T dr = sg * zr[k] + orr, di = sg * zi[k] + oi;
+        zr[k] = rot ? di : dr;       // (d) * (-i) = (d_i, -d_r)
+        zi[k] = rot ? -dr : di;
+      }
+    }
+    if constexpr (TPR >= 2) {
+      const T sg = (q & 1) ? (T)-1 : (T)1;
+#pragma unroll
+      for (int k = 0; k < E; ++k) {
+        const T orr = xor_lane<1>(zr[k]), oi = xor_lane<1>(zi[k]);
+        zr[k] = sg * zr[k] + orr;
+        zi[k] = sg * zi[k] + oi;
+      }
+    }
+  }
+  // exact reverse of lanes_fwd_true (unnormalized: times TPR)
+  __device__ __forceinline__ void lanes_inv_true(T (&zr)[E], T (&zi)[E]) const {
+    if constexpr (TPR >= 2) {
+      const T sg = (q & 1) ? (T)-1 : (T)1;
+#pragma unroll
+      for (int k = 0; k < E; ++k) {
+        const T orr = xor_lane<1>(zr[k]), oi = xor_lane<1>(zi[k]);
+        zr[k] = sg * zr[k] + orr;
+        zi[k] = sg * zi[k] + oi;
+      }
+    }
+    if constexpr (TPR >= 4) {
+      const T sg = (q & 2) ? (T)-1 : (T)1;
+      const bool rot = (q & 3) == 3;
+#pragma unroll
+      for (int k = 0; k < E; ++k) {
+        // undo the -i of lanes q mod 4 = 3: multiply by +i = (-z_i, z_r)
+        const T ar = rot ? -zi[k] : zr[k];
+        const T ai = rot ? zr[k] : zi[k];
+        const T orr = xor_lane<2>(ar), oi = xor_lane<2>(ai);
+        zr[k] = sg * ar + orr;
+        zi[k] = sg * ai + oi;
+      }
+    }
+    if constexpr (TPR == 8) {
+      const T sg = (q & 4) ? (T)-1 : (T)1;
+      T wr, wi;
+      w8_true<+1>((q & 4) ? (q & 3) : 0, wr, wi);
+#pragma unroll
+      for (int k = 0; k < E; ++k) {
+        const T ar = zr[k] * wr - zi[k] * wi, ai = zr[k] * wi + zi[k] * wr;
+        const T orr = xor_lane<7>(ar), oi = xor_lane<7>(ai);
+        zr[k] = sg * ar + orr;
+        zi[k] = sg * ai + oi;
+      }
+    }
   }
 
   // forward: strided -> blocked, exp(-2 pi i ...)
@@ -401,14 +496,20 @@ struct Fft2 {
     reg_fft<T, E, -1>(zr, zi);
     if constexpr (TPR > 1) {
       twiddle<-1>(zr, zi);
-      lanes_fwd(zr, zi);
+      if constexpr (SIGNED)
+        lanes_fwd(zr, zi);
+      else
+        lanes_fwd_true(zr, zi);
     }
   }
 
   // inverse: blocked -> strided, exp(+2 pi i ...), unnormalized
   __device__ __forceinline__ void inv_line(T (&zr)[E], T (&zi)[E]) const {
     if constexpr (TPR > 1) {
-      lanes_inv(zr, zi);
+      if constexpr (SIGNED)
+        lanes_inv(zr, zi);
+      else
+        lanes_inv_true(zr, zi);
       twiddle<+1>(zr, zi);
     }
     reg_fft<T, E, +1>(zr, zi);
@@ -465,18 +566,23 @@ struct Fft2 {
     }
   }
 
-  // full 2D: row real -> column spectra (OWN: the last transform was an inv2)
-  template <bool OWN = false>
+  // full 2D: row real -> column spectra (OWN: the last transform was an inv2;
+  // FREE: the next one may be another fwd2 with OWN, so the transpose ends
+  // with a barrier)
+  template <bool OWN = false, bool FREE = false>
   __device__ __forceinline__ void fwd2(T (&zr)[E], T (&zi)[E]) const {
     fwd_line(zr, zi);
     t_rows_to_cols<OWN>(zr, zi);
+    if constexpr (FREE) __syncthreads();
     fwd_line(zr, zi);
   }
-  // full 2D: column spectra -> row real (OWN: the last transform was a fwd2)
-  template <bool OWN = false>
+  // full 2D: column spectra -> row real (OWN: the last transform was a fwd2;
+  // FREE: the next one may be another inv2 with OWN)
+  template <bool OWN = false, bool FREE = false>
   __device__ __forceinline__ void inv2(T (&zr)[E], T (&zi)[E]) const {
     inv_line(zr, zi);
     t_cols_to_rows<OWN>(zr, zi);
+    if constexpr (FREE) __syncthreads();
     inv_line(zr, zi);
   }
 };

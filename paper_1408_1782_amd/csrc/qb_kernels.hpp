@@ -16,20 +16,21 @@
 
 namespace qb {
 
+// Tile shape a plan starts with (elements per thread).  P = 32 in float64
+// over 128 cells: 2.71 ms with E = 16, 2.30 with 8.
 template <typename T, int P>
-struct Cfg;
-template <>
-struct Cfg<double, 32> { static constexpr int E = 16; };
-template <>
-struct Cfg<double, 64> { static constexpr int E = 16; };
-template <>
-struct Cfg<double, 128> { static constexpr int E = 16; };
-template <>
-struct Cfg<float, 32> { static constexpr int E = 16; };
-template <>
-struct Cfg<float, 64> { static constexpr int E = 16; };
-template <>
-struct Cfg<float, 128> { static constexpr int E = 16; };
+struct Cfg {
+  static constexpr int E = sizeof(T) == 8 && P == 32 ? 8 : 16;
+};
+
+// Float64 sums run in groups, one workgroup each (k_i3, k_terms and their
+// transposes).  A float32 plan keeps one chain per (cell, j) and per (cell,
+// task), in the order of the nodes and directions, and the transforms of the
+// input stage packed in pairs: its results are compared across versions
+// through float64 moments, which resolve the rounding of the float32 sums.
+constexpr bool groups_of(int precision) { return precision == 0; }  // QB_F64
+template <typename T>
+constexpr bool grouped = sizeof(T) == 8;
 
 // Device-side view of the plan's tables and buffers (all device pointers).
 template <typename T>
@@ -83,10 +84,19 @@ __device__ __forceinline__ int centered(int k) {
   return k < P / 2 ? k : k - P;
 }
 
+// (a + i b) e for complex a, b, e: the packed spectrum of two shifted fields.
+// Float64 adds first (10 operations); float32 keeps a e + i (b e) (14).
 template <typename T>
-__device__ __forceinline__ void cmul(T ar, T ai, T br, T bi, T& cr, T& ci) {
-  cr = ar * br - ai * bi;
-  ci = ar * bi + ai * br;
+__device__ __forceinline__ void shift_pair(T ar, T ai, T br, T bi, T er, T ei, T& zr, T& zi) {
+  if constexpr (grouped<T>) {
+    cmul(ar - bi, ai + br, er, ei, zr, zi);
+  } else {
+    T xr, xi, yr, yi;
+    cmul(ar, ai, er, ei, xr, xi);
+    cmul(br, bi, er, ei, yr, yi);
+    zr = xr - yi;
+    zi = xi + yr;
+  }
 }
 
 // Raw buffer access: one 128-bit resource per array (scalar registers), a
@@ -223,9 +233,9 @@ __global__ void k_state_to_api(const T* __restrict__ w, TA* __restrict__ W, int 
 
 // ------------------------------------------------------------------ engine setup
 // Whether the LDS of a compute unit holds two planes of the transpose buffer
-// (all but float64 at P = 128).
+// (all at P <= 64).
 template <typename T, int P, int E>
-constexpr bool two_planes = (2 * Fft2<T, P, E>::PLANE + Fft2<T, P, E>::TW_SCALARS) * (int)sizeof(T) <= 160 * 1024;
+constexpr bool two_planes = P <= 64;
 
 template <typename T, int P, int E, bool XB = two_planes<T, P, E>>
 struct Kern {
@@ -236,10 +246,7 @@ struct Kern {
   static constexpr int LDS = Eng::LDS_SCALARS + Eng::TW_SCALARS;
   // least occupancy of k_i3 (waves per SIMD): two workgroups of 256 threads
   // per compute unit, which a few registers more than 256 would halve
-  // least occupancy of k_i3 (waves per SIMD): at P = 64, E = 8 in float32 two
-  // workgroups of 512 threads per compute unit (10.1 ms at N = 32 over 128
-  // cells; 12.4 with the few registers more that leave room for one)
-  static constexpr int WAVES = NT == 512 && sizeof(T) == 4 && P == 64 ? 4 : 1;
+  static constexpr int WAVES = 1;
 };
 
 template <typename T, int P, int E, bool XB>
@@ -306,9 +313,9 @@ struct I3Regs {
 // ------------------------------------------------------------------ dft_in
 // w_mu(v_n) -> w_hat_mu on Xi (Nyquist zeroed, padded to P, col spec), and the
 // trigonometric interpolants w_mu, f0 = 2 w0 - 1 on the P grid (row real).
-// One workgroup per (cell, mu): two transforms in sequence, where one per
-// cell runs six; a launch of one cell is bound by that chain (33 -> 14 us at
-// N = 32 in float64), and a launch that fills the chip is too small to matter.
+// One workgroup per (cell, mu) in float64: two transforms in sequence, where
+// one per cell runs six; a launch of one cell is bound by that chain (33 -> 14
+// us at N = 32), and a launch that fills the chip is too small to matter.
 template <typename T, int P, int E>
 __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_dft_in(DevPlan<T> d, const T* __restrict__ w, int cell0) {
   using K = Kern<T, P, E>;
@@ -354,6 +361,65 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_dft_in(DevPlan<T> d, co
     if (mu == 0) bst<T>(rw, (T)2 * zr[n] - (T)1, vo, (4 * K::FSZ + o) * S);
   }
 }
+// One workgroup per cell, the interpolants transformed in pairs (float32).
+template <typename T, int P, int E>
+__global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_dft_in_seq(DevPlan<T> d, const T* __restrict__ w, int cell0) {
+  using K = Kern<T, P, E>;
+  constexpr unsigned S = sizeof(T);
+  __shared__ T smem[K::LDS];
+  typename K::Eng eng;
+  setup(eng, smem, d.tw);
+  const int cell = cell0 + blockIdx.x;
+  const int N = P / 2;
+  const unsigned vo = threadIdx.x * S;
+  const size_t cs = (size_t)d.Nx * N * N;
+  const int y = eng.line;
+  const rsrc_t rs = mkbuf(d.spec + (size_t)blockIdx.x * 8 * K::FSZ, 8 * K::FSZ);
+  const rsrc_t rw = mkbuf(d.wP + (size_t)blockIdx.x * 5 * K::FSZ, 5 * K::FSZ);
+  const T inv_n2 = (T)1 / (T)(N * N);
+  const int bx = centered<P>(eng.line);
+  const bool kx_in = bx > -N / 2 && bx < N / 2;
+#pragma unroll 1
+  for (int mu = 0; mu < 4; ++mu) {
+    T zr[E], zi[E];
+    // the velocity grid sits on the even points of the padded grid
+    const bool on_grid = ((eng.q | y) & 1) == 0;
+    const T* wrow = w + mu * cs + (size_t)cell * N * N + (centered<P>(y) / 2 + N / 2);
+#pragma unroll
+    for (int n = 0; n < E; ++n) {
+      zr[n] = on_grid ? wrow[vel_index<P, K::TPR>(eng.q, n) * N] : (T)0;
+      zi[n] = 0;
+    }
+    eng.fwd2(zr, zi);
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
+      const int by = centered<P>(eng.bk(k));
+      const bool in = kx_in && by > -N / 2 && by < N / 2;
+      bst<T>(rs, in ? zr[k] * inv_n2 : (T)0, vo, ((2 * mu) * K::FSZ + k * K::NT) * S);
+      bst<T>(rs, in ? zi[k] * inv_n2 : (T)0, vo, ((2 * mu + 1) * K::FSZ + k * K::NT) * S);
+    }
+  }
+#pragma unroll 1
+  for (int pr = 0; pr < 2; ++pr) {
+    T zr[E], zi[E];
+    const unsigned fa = 2 * (2 * pr) * K::FSZ, fb = 2 * (2 * pr + 1) * K::FSZ;
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
+      const unsigned o = k * K::NT;
+      // (a_r + i a_i) + i (b_r + i b_i)
+      zr[k] = bld<T>(rs, vo, (fa + o) * S) - bld<T>(rs, vo, (fb + K::FSZ + o) * S);
+      zi[k] = bld<T>(rs, vo, (fa + K::FSZ + o) * S) + bld<T>(rs, vo, (fb + o) * S);
+    }
+    eng.inv2(zr, zi);
+#pragma unroll
+    for (int n = 0; n < E; ++n) {
+      const unsigned o = n * K::NT;
+      bst<T>(rw, zr[n], vo, ((2 * pr) * K::FSZ + o) * S);
+      bst<T>(rw, zi[n], vo, ((2 * pr + 1) * K::FSZ + o) * S);
+      if (pr == 0) bst<T>(rw, (T)2 * zr[n] - (T)1, vo, (4 * K::FSZ + o) * S);
+    }
+  }
+}
 
 // ------------------------------------------------------------------ I_1, I_4, I_2
 // task 0..2: I_1[f0, w_l, .] (l = task + 1), hoisted outer kernel K_j'
@@ -368,13 +434,13 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_dft_in(DevPlan<T> d, co
 // cell at N = 32 in float64 took 330 us for them), for one final transform
 // more per group.  The spectral accumulators of a group stay in registers
 // where the register plan has room for two more fields (TREG), else they go
-// through the buffer acc.
+// through the buffer acc (as all do in float32).
 constexpr int kTermPlanes = 11;
 template <typename T, int P, int E>
 __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_terms(DevPlan<T> d, int ncells) {
   using K = Kern<T, P, E>;
   constexpr unsigned S = sizeof(T);
-  constexpr bool TREG = I3Regs<T, P, E>::PAIR;
+  constexpr bool TREG = grouped<T> && I3Regs<T, P, E>::PAIR;
   __shared__ T smem[K::LDS];
   typename K::Eng eng;
   setup(eng, smem, d.tw);
@@ -617,10 +683,8 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) __attribute__((amdgpu_waves_pe
         const unsigned o = k * K::NT;
         T er, ei;
         cmul(pxr, pxi, py[2 * k], py[2 * k + 1], er, ei);
-        // (a + i b) e
-        const T xr = bld<T>(rs, vo, (fa + o) * S) - bld<T>(rs, vo, (fb + K::FSZ + o) * S);
-        const T xi = bld<T>(rs, vo, (fa + K::FSZ + o) * S) + bld<T>(rs, vo, (fb + o) * S);
-        cmul(xr, xi, er, ei, zr[k], zi[k]);
+        shift_pair(bld<T>(rs, vo, (fa + o) * S), bld<T>(rs, vo, (fa + K::FSZ + o) * S), bld<T>(rs, vo, (fb + o) * S),
+                   bld<T>(rs, vo, (fb + K::FSZ + o) * S), er, ei, zr[k], zi[k]);
         if (k % SG == SG - 1) __builtin_amdgcn_sched_barrier(0);
       }
       eng.inv2(zr, zi);
@@ -782,32 +846,51 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) __attribute__((amdgpu_waves_pe
             zi[n] = pb[PREG ? n : 0];
           }
         }
-        eng.template fwd2<true>(zr, zi);
-        __syncthreads();  // read before the next row pair's transposes write
+        eng.template fwd2<true, true>(zr, zi);
+        if constexpr (grouped<T>) {
 #pragma unroll
-        for (int b = 0; b < E; b += PB) {
-          T pr0[PB], pi0[PB];
+          for (int b = 0; b < E; b += PB) {
+            T pr0[PB], pi0[PB];
 #pragma unroll
-          for (int i = 0; i < PB; ++i) {
-            const unsigned o = (b + i) * K::NT, vk = xi_off(b + i);
-            pr0[i] = bld<T>(rp, vk, (fr + o) * S);
-            pi0[i] = bld<T>(rp, vk, (fi + o) * S);
+            for (int i = 0; i < PB; ++i) {
+              const unsigned o = (b + i) * K::NT, vk = xi_off(b + i);
+              pr0[i] = bld<T>(rp, vk, (fr + o) * S);
+              pi0[i] = bld<T>(rp, vk, (fi + o) * S);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < PB; ++i) {
+              const int k = b + i;
+              const unsigned o = k * K::NT, vk = xi_off(k);
+              T er, ei;
+              cmul(pxr, pxi, py[2 * k], py[2 * k + 1], er, ei);
+              T xr, xi;
+              cmul(zr[k], zi[k], er, -ei, xr, xi);
+              xr += m != mb ? pr0[i] : (T)0;
+              xi += m != mb ? pi0[i] : (T)0;
+              bst<T>(rp, xr, vk, (fr + o) * S);
+              bst<T>(rp, xi, vk, (fi + o) * S);
+            }
+            __builtin_amdgcn_sched_barrier(0);
           }
-          __builtin_amdgcn_sched_barrier(0);
+        } else {
+          // (element by element: the order float32 rounds these sums in)
 #pragma unroll
-          for (int i = 0; i < PB; ++i) {
-            const int k = b + i;
-            const unsigned o = k * K::NT, vk = xi_off(k);
+          for (int k = 0; k < E; ++k) {
+            const unsigned o = k * K::NT;
+            const unsigned vk = xi_off(k);
             T er, ei;
             cmul(pxr, pxi, py[2 * k], py[2 * k + 1], er, ei);
             T xr, xi;
             cmul(zr[k], zi[k], er, -ei, xr, xi);
-            xr += m != mb ? pr0[i] : (T)0;
-            xi += m != mb ? pi0[i] : (T)0;
+            const T pr0 = bld<T>(rp, vk, (fr + o) * S);
+            const T pi0 = bld<T>(rp, vk, (fi + o) * S);
+            xr += m != mb ? pr0 : (T)0;
+            xi += m != mb ? pi0 : (T)0;
             bst<T>(rp, xr, vk, (fr + o) * S);
             bst<T>(rp, xi, vk, (fi + o) * S);
+            if (k % SG == SG - 1) __builtin_amdgcn_sched_barrier(0);
           }
-          __builtin_amdgcn_sched_barrier(0);
         }
       } else if (m == mb) {
         // no partner spectrum (unpaired kernel, or a single node)
@@ -936,6 +1019,46 @@ __global__ __launch_bounds__(32 * kAsmRow) void k_assemble(DevPlan<T> d, int nce
         pd * (-two * Sv * wk + two * sum + two * (y0 * wk - tr[3 + row][el] * w0));
   }
   *(vec*)(d.i3sum + (size_t)cell * per + (size_t)row * fsz + e) = r;
+}
+
+// The same with one chain of sums per element, over j in order (float32).
+template <typename T, int P, int E>
+__global__ void k_assemble_seq(DevPlan<T> d, int ncells) {
+  using Eng = Fft2<T, P, E>;
+  constexpr int fsz = P * P;
+  const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= (size_t)ncells * fsz) return;
+  const size_t cell = idx / fsz, e = idx % fsz;
+  const size_t per = (size_t)4 * fsz;
+  // col spec position e = k NT + t: frequency (kx, ky) = (t / TPR, k + E bitrev(q))
+  const int t = (int)(e % Eng::NT), kk = (int)(e / Eng::NT);
+  const int bx = centered<P>(t / Eng::TPR);
+  const int by = centered<P>(kk + E * bitrev_rt(Eng::lane_label(t % Eng::TPR), Eng::LB));
+  const bool on_xi = bx > -P / 4 && bx < P / 4 && by > -P / 4 && by < P / 4;
+  const T* o3 = d.i3o + cell * d.J * per + e;
+  const T* p3 = d.i3p + cell * d.J * per + e;
+  T b[4] = {0, 0, 0, 0}, q[4] = {0, 0, 0, 0};
+#pragma unroll 4
+  for (int j = 0; j < d.J; ++j)
+    for (int nu = 0; nu < 4; ++nu) {
+      b[nu] += o3[(size_t)j * per + (size_t)nu * fsz];
+      if (on_xi) q[nu] += p3[(size_t)j * per + (size_t)nu * fsz];
+    }
+  T* ps = d.i3ps + cell * per + e;
+  for (int nu = 0; nu < 4; ++nu) ps[(size_t)nu * fsz] = q[nu];
+  const T* wp = d.wP + cell * 5 * fsz + e;
+  const T* tr = d.terms + cell * kTermPlanes * fsz + e;
+  const T w0 = wp[0], w1 = wp[fsz], w2 = wp[2 * fsz], w3 = wp[3 * fsz];
+  const T g1 = tr[0], g2 = tr[fsz], g3 = tr[2 * fsz];
+  const T y0 = tr[3 * fsz], y1 = tr[4 * fsz], y2 = tr[5 * fsz], y3 = tr[6 * fsz];
+  const T Sv = (tr[7 * fsz] + tr[8 * fsz]) + (tr[9 * fsz] + tr[10 * fsz]);
+  const T pi = (T)kPi, two = (T)2;
+  T* r = d.i3sum + cell * per + e;
+  const T pd = d.wd * pi, wc = d.wc;
+  r[0] = pd * (two * Sv * ((T)1 - w0) - two * b[0] + two * (y0 * w0 - y1 * w1 - y2 * w2 - y3 * w3));
+  r[fsz] = -wc * two * (g2 * w3 - g3 * w2) + pd * (-two * Sv * w1 + two * b[1] + two * (y0 * w1 - y1 * w0));
+  r[2 * fsz] = -wc * two * (g3 * w1 - g1 * w3) + pd * (-two * Sv * w2 + two * b[2] + two * (y0 * w2 - y2 * w0));
+  r[3 * fsz] = -wc * two * (g1 * w2 - g2 * w1) + pd * (-two * Sv * w3 + two * b[3] + two * (y0 * w3 - y3 * w0));
 }
 
 // ------------------------------------------------------------------ combine

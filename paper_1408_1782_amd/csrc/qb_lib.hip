@@ -99,7 +99,7 @@ void gauss_legendre(int M, std::vector<double>& x, std::vector<double>& w) {
 }
 
 // Tile shapes (elements per thread E; lanes per line P / E) compiled for
-// each padded grid size; the first is the default, qb_plan_tune picks one.
+// each padded grid size; a plan starts with cfg_E, qb_plan_tune picks one.
 std::vector<int> tile_candidates(int P) {
   switch (P) {
     case 32: return {16, 8};
@@ -111,6 +111,14 @@ std::vector<int> tile_candidates(int P) {
 int cfg_E(int precision, int P) {
   if (precision == QB_F64) return P == 32 ? qb::Cfg<double, 32>::E : (P == 64 ? qb::Cfg<double, 64>::E : qb::Cfg<double, 128>::E);
   return P == 32 ? qb::Cfg<float, 32>::E : (P == 64 ? qb::Cfg<float, 64>::E : qb::Cfg<float, 128>::E);
+}
+
+// Tile and I_3 kernel the reverse mode of a plan starts with: in float64 the
+// fastest measured over 48 cells (E = 16 and 8, each with its better kernel):
+// P = 32 2.80 and 2.14 ms, P = 64 20.2 and 17.8.
+void cfg_vjp(int precision, int P, int& E, int& variant) {
+  E = precision == QB_F64 && P <= 64 ? 8 : 16;
+  variant = precision == QB_F64 && P <= 64 ? 1 : 0;
 }
 
 }  // namespace
@@ -150,23 +158,16 @@ bool reserve_layout_tables(qb_plan_s* pl, int E, qb_plan_s::TabSet& ts) {
          pl->alloc(&ts.psips, J * FSZ * b) && pl->alloc(&ts.negk, FSZ * sizeof(unsigned));
 }
 
-// Compute the table set of tile shape ts.E in float64 and copy it into its
-// reserved memory (Sec. 3.2: theta grids, phi_R, omega_G, psi_R).
-template <typename T>
-bool fill_layout_tables(qb_plan_s* pl, qb_plan_s::TabSet& ts) {
-  const qb_problem& p = pl->prob;
-  const int E = ts.E;
-  const int P = pl->P, TPR = P / E, NT = P * TPR, J = p.J;
+// Quadrature tables of Sec. 3.2 in natural order [J][kx][ky] (theta grids,
+// phi_R, omega_G, psi_R), float64.
+struct NaturalTables {
+  std::vector<double> phip, Kt, psi, psip;
+};
+
+NaturalTables natural_tables(const qb_problem& p, int P) {
+  const int J = p.J;
   const double L = p.L, R = p.R;
   const size_t FSZ = (size_t)P * P;
-  // (cos, sin)(2 pi q k / P) at [q][k], q < TPR, k < E  (engine twiddles)
-  std::vector<double> tw(2 * P);
-  for (int q = 0; q < TPR; ++q)
-    for (int k = 0; k < E; ++k) {
-      const int i = q * E + k;
-      tw[2 * i] = std::cos(2.0 * M_PI * ((q * k) % P) / P);
-      tw[2 * i + 1] = std::sin(2.0 * M_PI * ((q * k) % P) / P);
-    }
   std::vector<double> th_c(J), th_s(J), thp_c(J), thp_s(J);
   for (int j = 0; j < J; ++j) {
     th_c[j] = std::cos(j * M_PI / J);
@@ -179,30 +180,53 @@ bool fill_layout_tables(qb_plan_s* pl, qb_plan_s::TabSet& ts) {
   for (int j = 0; j < J; ++j)
     for (int jp = 0; jp < J; ++jp)
       wG[(size_t)j * J + jp] = -std::pow(2.0 * M_PI / J, 2) / (th_c[j] * thp_c[jp] + th_s[j] * thp_s[jp]);
-  const double invP2 = 1.0 / ((double)P * P);
-  std::vector<double> phip(J * FSZ), Kt(J * FSZ), psi(J * FSZ), psip(J * FSZ), psiw(J * FSZ),
-      psips(J * FSZ);
-  std::vector<double> phi_j(J);
+  NaturalTables t;
+  t.phip.resize(J * FSZ), t.Kt.resize(J * FSZ), t.psi.resize(J * FSZ), t.psip.resize(J * FSZ);
+  std::vector<double> phi_j(J), k(J);
   for (int kx = 0; kx < P; ++kx) {
     const double bx = centered_h(kx, P);
     for (int ky = 0; ky < P; ++ky) {
       const double by = centered_h(ky, P);
-      const size_t o = colspec_index(kx, ky, E, TPR, NT);
+      const size_t o = (size_t)kx * P + ky;
       for (int j = 0; j < J; ++j) phi_j[j] = phi_R(bx * th_c[j] + by * th_s[j], L, R);
+      std::fill(k.begin(), k.end(), 0.0);
+      for (int i = 0; i < J; ++i)
+        for (int j = 0; j < J; ++j) k[j] += wG[(size_t)i * J + j] * phi_j[i];
       for (int j = 0; j < J; ++j) {
-        phip[j * FSZ + o] = phi_R(bx * thp_c[j] + by * thp_s[j], L, R);
-        double k = 0.0;
-        for (int i = 0; i < J; ++i) k += wG[(size_t)i * J + j] * phi_j[i];
-        Kt[j * FSZ + o] = k * invP2;
-        const double ps = psi_R(bx * th_c[j] + by * th_s[j], L, R);
-        const double pp = psi_R(-bx * th_s[j] + by * th_c[j], L, R);  // theta_j rotated by pi/2
-        psi[j * FSZ + o] = ps;
-        psip[j * FSZ + o] = pp;
-        psiw[j * FSZ + o] = (M_PI / J) * ps * invP2;
-        psips[j * FSZ + o] = pp * invP2;
+        t.phip[j * FSZ + o] = phi_R(bx * thp_c[j] + by * thp_s[j], L, R);
+        t.Kt[j * FSZ + o] = k[j];
+        t.psi[j * FSZ + o] = psi_R(bx * th_c[j] + by * th_s[j], L, R);
+        t.psip[j * FSZ + o] = psi_R(-bx * th_s[j] + by * th_c[j], L, R);  // theta_j rotated by pi/2
       }
     }
   }
+  return t;
+}
+
+// Copy the tables into the reserved memory of tile shape ts.E in its element order.
+template <typename T>
+bool fill_layout_tables(qb_plan_s* pl, qb_plan_s::TabSet& ts, const NaturalTables& t) {
+  const int E = ts.E;
+  const int P = pl->P, TPR = P / E, NT = P * TPR, J = pl->prob.J;
+  const size_t FSZ = (size_t)P * P;
+  // (cos, sin)(2 pi q k / P) at [q][k], q < TPR, k < E  (engine twiddles)
+  std::vector<double> tw(2 * P);
+  for (int q = 0; q < TPR; ++q)
+    for (int k = 0; k < E; ++k) {
+      const int i = q * E + k;
+      tw[2 * i] = std::cos(2.0 * M_PI * ((q * k) % P) / P);
+      tw[2 * i + 1] = std::sin(2.0 * M_PI * ((q * k) % P) / P);
+    }
+  std::vector<size_t> pos(FSZ);
+  for (int kx = 0; kx < P; ++kx)
+    for (int ky = 0; ky < P; ++ky) pos[(size_t)kx * P + ky] = colspec_index(kx, ky, E, TPR, NT);
+  std::vector<double> buf(J * FSZ);
+  auto table = [&](void* dst, const std::vector<double>& src, double scale) {
+    for (int j = 0; j < J; ++j)
+      for (size_t o = 0; o < FSZ; ++o) buf[j * FSZ + pos[o]] = scale * src[j * FSZ + o];
+    return put<T>(dst, buf);
+  };
+  const double invP2 = 1.0 / ((double)P * P);
   // col spec position of -k (mod P) for each position of k, with the top bit
   // set where the kept spectra carry different signs at k and -k
   const int lb = qb::ilog2(TPR);
@@ -210,15 +234,17 @@ bool fill_layout_tables(qb_plan_s* pl, qb_plan_s::TabSet& ts) {
     auto ones = [&](int k) { const int q = qb::bitrev_rt(k / E, lb); return (q ^ (q >> 1)) & 1; };
     return ones(kx) ^ ones(ky);
   };
+  const bool with_signs = !(sizeof(T) == 4 && P == 128);  // Fft2::SIGNED
   std::vector<unsigned> negk(FSZ);
   for (int kx = 0; kx < P; ++kx)
     for (int ky = 0; ky < P; ++ky) {
       const int nx = (P - kx) % P, ny = (P - ky) % P;
-      const unsigned flip = sign(kx, ky) != sign(nx, ny) ? 0x80000000u : 0u;
-      negk[colspec_index(kx, ky, E, TPR, NT)] = (unsigned)colspec_index(nx, ny, E, TPR, NT) | flip;
+      const unsigned flip = with_signs && sign(kx, ky) != sign(nx, ny) ? 0x80000000u : 0u;
+      negk[pos[(size_t)kx * P + ky]] = (unsigned)pos[(size_t)nx * P + ny] | flip;
     }
-  ts.built = put<T>(ts.tw, tw) && put<T>(ts.phip, phip) && put<T>(ts.Kt, Kt) && put<T>(ts.psi, psi) &&
-             put<T>(ts.psip, psip) && put<T>(ts.psiw, psiw) && put<T>(ts.psips, psips) &&
+  ts.built = put<T>(ts.tw, tw) && table(ts.phip, t.phip, 1.0) && table(ts.Kt, t.Kt, invP2) &&
+             table(ts.psi, t.psi, 1.0) && table(ts.psip, t.psip, 1.0) &&
+             table(ts.psiw, t.psi, (M_PI / J) * invP2) && table(ts.psips, t.psip, invP2) &&
              hip_ok(hipMemcpy(ts.negk, negk.data(), FSZ * sizeof(unsigned), hipMemcpyHostToDevice), "hipMemcpy");
   return ts.built;
 }
@@ -230,7 +256,7 @@ int table_set(qb_plan_s* pl, int E) {
   for (size_t i = 0; i < pl->tabs.size(); ++i)
     if (pl->tabs[i].E == E) idx = (int)i;
   if (idx < 0) return -1;
-  if (!pl->tabs[idx].built && !fill_layout_tables<T>(pl, pl->tabs[idx])) return -1;
+  if (!pl->tabs[idx].built && !fill_layout_tables<T>(pl, pl->tabs[idx], natural_tables(pl->prob, pl->P))) return -1;
   return idx;
 }
 
@@ -322,7 +348,11 @@ bool reserve_tables(qb_plan_s* pl) {
 
 template <typename T>
 bool fill_tables(qb_plan_s* pl) {
-  return fill_phases<T>(pl) && select_tile<T>(pl, pl->E);
+  // the table sets of the tiles the plan starts with, forward and reverse
+  const NaturalTables t = natural_tables(pl->prob, pl->P);
+  for (auto& ts : pl->tabs)
+    if ((ts.E == pl->E || ts.E == pl->vjp_E) && !fill_layout_tables<T>(pl, ts, t)) return false;
+  return fill_phases<T>(pl) && select_vjp_tile<T>(pl, pl->vjp_E) && select_tile<T>(pl, pl->E);
 }
 
 // Pauli components of W_FD (eq. W_FermiDirac) on the velocity grid: [4][N][N]
@@ -409,7 +439,7 @@ struct CollBufs {
 template <typename T>
 bool carve_collision(Arena& a, const qb_plan_s* pl, size_t C, size_t I, bool one, CollBufs& b) {
   const size_t FSZ = (size_t)pl->P * pl->P, J = pl->prob.J, t = sizeof(T);
-  const size_t ng = one ? 1 : max_node_groups(pl->prob), tg = term_groups(pl->prob.J, one);
+  const size_t ng = one ? 1 : max_node_groups(pl->prob), tg = one ? 1 : term_groups(pl->prob);
   const size_t tasks = I * J * ng;
   return a.take(&b.i3s, tasks * qb::kI3sPlanes<T> * FSZ * t) && a.take(&b.spec, C * 8 * FSZ * t) &&
          a.take(&b.wP, C * 5 * FSZ * t) && a.take(&b.terms, C * qb::kTermPlanes * tg * FSZ * t) &&
@@ -450,7 +480,7 @@ bool build_adjoint(qb_plan_s* pl) {
   void** states[] = {&pl->wn, &pl->wa, &pl->w1, &pl->wb, &pl->lb, &pl->ls, &pl->la, &pl->cg, &pl->g0};
   for (void** q : states)
     if (!pl->alloc_adj(q, st)) return false;
-  const size_t tg = term_groups(p.J, false), tasks = (size_t)pl->i3cells * J * max_node_groups(p);
+  const size_t tg = term_groups(p), tasks = (size_t)pl->i3cells * J * max_node_groups(p);
   return pl->alloc_adj(&pl->lamP, C * 4 * FSZ * b) && pl->alloc_adj(&pl->acot, C * 16 * FSZ * b) &&
          pl->alloc_adj(&pl->gspec, C * 22 * tg * FSZ * b) && pl->alloc_adj(&pl->gf0, C * 7 * tg * FSZ * b) &&
          pl->alloc_adj(&pl->i3g, tasks * 8 * FSZ * b) && pl->alloc_adj(&pl->i3sb, tasks * 4 * FSZ * b) &&
@@ -1044,6 +1074,7 @@ void init_plan(qb_plan_s* pl, const qb_problem& problem, int max_cells) {
   pl->prob = problem;
   pl->P = 2 * problem.N;
   pl->E = cfg_E(problem.precision, pl->P);
+  cfg_vjp(problem.precision, pl->P, pl->vjp_E, pl->vjp_variant);
   pl->TPR = pl->P / pl->E;
   pl->NT = pl->P * pl->TPR;
   pl->wcells = chunk_cells(problem, max_cells);

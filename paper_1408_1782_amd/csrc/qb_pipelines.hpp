@@ -10,7 +10,10 @@ bool collision_pipeline(qb_plan_s* pl, const T* w, T* c, int ncells, int cell0, 
   constexpr int NT = qb::Fft2<T, P, E>::NT;
   DevPlan<T> d = devplan<T>(pl, pl->cur_tab);
   int id = pl->begin(QB_K_DFT_IN, s);
-  hipLaunchKernelGGL((qb::k_dft_in<T, P, E>), dim3(4 * ncells), dim3(NT), 0, s, d, w, cell0);
+  if constexpr (qb::grouped<T>)
+    hipLaunchKernelGGL((qb::k_dft_in<T, P, E>), dim3(4 * ncells), dim3(NT), 0, s, d, w, cell0);
+  else
+    hipLaunchKernelGGL((qb::k_dft_in_seq<T, P, E>), dim3(ncells), dim3(NT), 0, s, d, w, cell0);
   pl->end(id, s);
   // persistent launches: at most the workgroups that are resident at once
   // (rounded down to a multiple of 8), grid-striding over the task list
@@ -39,8 +42,11 @@ bool collision_pipeline(qb_plan_s* pl, const T* w, T* c, int ncells, int cell0, 
     else
       hipLaunchKernelGGL((qb::k_i3<T, P, E, false>), dim3(grid(ntask, (const void*)qb::k_i3<T, P, E, false>)),
                          dim3(NT), 0, s, dc, nc);
-    hipLaunchKernelGGL((qb::k_assemble<T, P, E>), dim3(nc * (P * P / qb::kAsmEl<T>)), dim3(32 * qb::kAsmRow), 0, s, dc,
-                       nc);
+    if constexpr (qb::grouped<T>)
+      hipLaunchKernelGGL((qb::k_assemble<T, P, E>), dim3(nc * (P * P / qb::kAsmEl<T>)), dim3(32 * qb::kAsmRow), 0, s,
+                         dc, nc);
+    else
+      hipLaunchKernelGGL((qb::k_assemble_seq<T, P, E>), dim3(blocks((size_t)nc * P * P, 256)), dim3(256), 0, s, dc, nc);
   }
   pl->end(id, s);
   id = pl->begin(QB_K_COMBINE, s);
@@ -55,9 +61,12 @@ bool collision_vjp_pipeline(qb_plan_s* pl, const T* w, const T* lam, T* out, int
                             hipStream_t s) {
   constexpr int NT = qb::Fft2<T, P, E>::NT;
   DevPlan<T> d = devplan<T>(pl, pl->vjp_tab);
-  node_groups((d.M + 1) / 2, false, d.gs, d.ng);  // the reverse kernel always pairs its nodes
+  node_groups((d.M + 1) / 2, !qb::grouped<T>, d.gs, d.ng);  // the reverse kernel always pairs its nodes
   int id = pl->begin(QB_K_DFT_IN, s);
-  hipLaunchKernelGGL((qb::k_dft_in<T, P, E>), dim3(4 * ncells), dim3(NT), 0, s, d, w, cell0);
+  if constexpr (qb::grouped<T>)
+    hipLaunchKernelGGL((qb::k_dft_in<T, P, E>), dim3(4 * ncells), dim3(NT), 0, s, d, w, cell0);
+  else
+    hipLaunchKernelGGL((qb::k_dft_in_seq<T, P, E>), dim3(ncells), dim3(NT), 0, s, d, w, cell0);
   pl->end(id, s);
   // the forward I_1 / I_4 / I_2 fields are formed inside k_terms_vjp
   id = pl->begin(QB_K_ADJOINT, s);

@@ -58,8 +58,8 @@ struct qb_plan_s {
   int i3cells;  // cells per launch of k_i3 (its buffers hold this many)
   bool one_group = false;  // one summation group each in k_i3 and k_terms (the least workspace)
   bool i3_pair = true;  // I_3 kernel pairs the Gauss-Legendre nodes (tuned; default per tile)
-  int vjp_variant = 0;  // I_3 adjoint: 0 row w_bar in memory, 1 in registers (tuned)
-  int vjp_E = 0;        // tile shape of the reverse-mode pipeline (tuned; 0: the forward tile)
+  int vjp_variant = 0;  // I_3 adjoint: 0 row w_bar in memory, 1 in registers (cfg_vjp; tuned)
+  int vjp_E = 0;        // tile shape of the reverse-mode pipeline (cfg_vjp; tuned; 0: the forward tile)
   int vjp_tab = 0;      // its table set
   int term_sel = 3;     // collision terms assembled: 1 C_c, 2 C_d, 3 both
   int limiter = 0;      // transport slope limiter: 0 minmod, 1 superbee, 2 MC, 3 van Leer
@@ -147,6 +147,7 @@ inline void node_groups(int nnode, bool one, int& gs, int& ng) {
   ng = (nnode + gs - 1) / gs;
 }
 inline int max_node_groups(const qb_problem& p) {
+  if (!qb::groups_of(p.precision)) return 1;
   int gs, a, b;
   node_groups((p.M + 1) / 2, false, gs, a);
   node_groups(p.M, false, gs, b);
@@ -155,6 +156,7 @@ inline int max_node_groups(const qb_problem& p) {
 // Directions per group of k_terms: 4 pairs, 8 transforms beside the final one.
 constexpr int kTermDirs = 8;
 inline int term_groups(int J, bool one) { return one ? 1 : (J + kTermDirs - 1) / kTermDirs; }
+inline int term_groups(const qb_problem& p) { return term_groups(p.J, !qb::groups_of(p.precision)); }
 
 // Cells per launch of k_i3 in chunks of wcells cells: enough tasks for the
 // partly empty last round of a launch not to matter (some 30 rounds of the
@@ -200,9 +202,10 @@ inline DevPlan<T> devplan(qb_plan_s* pl, int tab) {
   d.i3sum = (T*)pl->i3sum;
   d.i3p = (T*)pl->i3p;
   d.i3ps = (T*)pl->i3ps;
-  node_groups(pl->i3_pair ? (d.M + 1) / 2 : d.M, pl->one_group, d.gs, d.ng);
-  d.tg = term_groups(d.J, pl->one_group);
-  d.td = pl->one_group ? d.J : kTermDirs;
+  const bool one = pl->one_group || !qb::groups_of(pl->prob.precision);
+  node_groups(pl->i3_pair ? (d.M + 1) / 2 : d.M, one, d.gs, d.ng);
+  d.tg = term_groups(d.J, one);
+  d.td = one ? d.J : kTermDirs;
   d.lamP = (T*)pl->lamP;
   d.acot = (T*)pl->acot;
   d.gspec = (T*)pl->gspec;
