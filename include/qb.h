@@ -106,6 +106,15 @@ typedef struct qb_plan_s* qb_plan;
  * state-sized buffers.  Pure host arithmetic; no HIP call. */
 size_t qb_workspace_bytes(const qb_problem* problem, int32_t max_cells);
 
+/* The workspace a plan runs fastest in (never less than qb_workspace_bytes).
+ * In float64 the sums over nodes and directions run in groups, one workgroup
+ * each, which need a buffer of their own: a plan of few cells is up to four
+ * times as fast with them.  A plan takes them if its workspace holds the
+ * groups of at least one cell beside the rest, else it sums in one group; the
+ * two differ in rounding only.  In float32 both sizes are equal.  Pure host
+ * arithmetic; no HIP call. */
+size_t qb_workspace_bytes_preferred(const qb_problem* problem, int32_t max_cells);
+
 /* Create a plan in the caller's device workspace (at least
  * qb_workspace_bytes(problem, max_cells) bytes, any alignment the HIP
  * allocator returns): validates the problem, builds the quadrature tables of
@@ -341,6 +350,9 @@ typedef struct qb_batch_s* qb_batch;
  * equal N must have equal M); 0 for an invalid batch. */
 size_t qb_batch_workspace_bytes(const qb_problem* problems, int32_t nprob);
 
+/* The same with every plan of the batch as in qb_workspace_bytes_preferred. */
+size_t qb_batch_workspace_bytes_preferred(const qb_problem* problems, int32_t nprob);
+
 /* Create a batch in the caller's device workspace (at least
  * qb_batch_workspace_bytes bytes; kept alive until qb_batch_destroy).
  * Allocates no device memory; creates one non-blocking HIP stream on which
@@ -388,6 +400,10 @@ qb_status qb_batch_step(qb_batch batch, void* const* W, const double* const* B, 
 /* Device bytes of the reverse-mode workspace of a plan (cotangent buffers
  * of the collision pipeline and of the states). */
 size_t qb_adjoint_workspace_bytes(qb_plan plan);
+
+/* The size the reverse mode runs fastest in, with summation groups as in
+ * qb_workspace_bytes_preferred (the same where the plan itself has none). */
+size_t qb_adjoint_workspace_bytes_preferred(qb_plan plan);
 
 /* Lay out the reverse-mode buffers in a caller workspace of at least
  * qb_adjoint_workspace_bytes(plan) bytes (kept alive until the plan is

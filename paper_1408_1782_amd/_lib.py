@@ -27,10 +27,13 @@ DIAG_NAMES = ("entropy", "entropy_production", "rel_entropy_global", "rel_entrop
 # names the header declares (checked by the CPU tests)
 EXPORTS = (
     "qb_workspace_bytes",
+    "qb_workspace_bytes_preferred",
     "qb_plan_create",
     "qb_plan_chunk_cells",
     "qb_adjoint_workspace_bytes",
+    "qb_adjoint_workspace_bytes_preferred",
     "qb_batch_workspace_bytes",
+    "qb_batch_workspace_bytes_preferred",
     "qb_plan_destroy",
     "qb_plan_bytes",
     "qb_collision",
@@ -119,16 +122,19 @@ def lib_path():
 def _declare(lib):
     vp, i32, dbl = ctypes.c_void_p, ctypes.c_int32, ctypes.c_double
     sz = ctypes.c_size_t
-    lib.qb_workspace_bytes.argtypes = [ctypes.POINTER(_Problem), i32]
-    lib.qb_workspace_bytes.restype = sz
+    for fn in (lib.qb_workspace_bytes, lib.qb_workspace_bytes_preferred):
+        fn.argtypes = [ctypes.POINTER(_Problem), i32]
+        fn.restype = sz
     lib.qb_plan_create.argtypes = [ctypes.POINTER(_Problem), i32, vp, sz, ctypes.POINTER(vp)]
     lib.qb_plan_create.restype = i32
     lib.qb_plan_chunk_cells.argtypes = [vp]
     lib.qb_plan_chunk_cells.restype = i32
-    lib.qb_adjoint_workspace_bytes.argtypes = [vp]
-    lib.qb_adjoint_workspace_bytes.restype = sz
-    lib.qb_batch_workspace_bytes.argtypes = [ctypes.POINTER(_Problem), i32]
-    lib.qb_batch_workspace_bytes.restype = sz
+    for fn in (lib.qb_adjoint_workspace_bytes, lib.qb_adjoint_workspace_bytes_preferred):
+        fn.argtypes = [vp]
+        fn.restype = sz
+    for fn in (lib.qb_batch_workspace_bytes, lib.qb_batch_workspace_bytes_preferred):
+        fn.argtypes = [ctypes.POINTER(_Problem), i32]
+        fn.restype = sz
     lib.qb_plan_destroy.argtypes = [vp]
     lib.qb_plan_destroy.restype = i32
     lib.qb_plan_bytes.argtypes = [vp]
@@ -309,11 +315,15 @@ def _dev(t, dtype, shape, name):
     return _ptr(t)
 
 
-def _workspace(nbytes):
-    """A device workspace of `nbytes` bytes (torch memory, 256-byte aligned)."""
+def _workspace(nbytes, least):
+    """A device workspace of `nbytes` bytes (torch memory, 256-byte aligned),
+    or of `least` bytes where there is no room for that."""
     import torch
 
-    return torch.empty(max(int(nbytes), 1), dtype=torch.uint8, device="cuda")
+    try:
+        return torch.empty(max(int(nbytes), 1), dtype=torch.uint8, device="cuda")
+    except torch.cuda.OutOfMemoryError:
+        return torch.empty(max(int(least), 1), dtype=torch.uint8, device="cuda")
 
 
 class Plan:
@@ -328,10 +338,10 @@ class Plan:
         self.problem = problem
         self.cdtype = torch.complex128 if problem.precision == "f64" else torch.complex64
         pc = problem._c()
-        nbytes = self.lib.qb_workspace_bytes(ctypes.byref(pc), int(max_cells))
-        if nbytes == 0:
+        least = self.lib.qb_workspace_bytes(ctypes.byref(pc), int(max_cells))
+        if least == 0:
             _check(QB_EINVAL, "qb_workspace_bytes")
-        self.ws = _workspace(nbytes)
+        self.ws = _workspace(self.lib.qb_workspace_bytes_preferred(ctypes.byref(pc), int(max_cells)), least)
         self.ws_adj = None
         h = ctypes.c_void_p()
         _check(self.lib.qb_plan_create(ctypes.byref(pc), int(max_cells), _ptr(self.ws), self.ws.numel(),
@@ -417,11 +427,11 @@ class Plan:
     # ------------------------------------------------------------ reverse mode
     def enable_adjoint(self):
         """qb_plan_enable_adjoint: lay out the reverse-mode buffers in a
-        workspace of qb_adjoint_workspace_bytes (once)."""
+        workspace of qb_adjoint_workspace_bytes_preferred (once)."""
         if self.ws_adj is not None:
             return
-        nbytes = self.lib.qb_adjoint_workspace_bytes(self.handle)
-        ws = _workspace(nbytes)
+        ws = _workspace(self.lib.qb_adjoint_workspace_bytes_preferred(self.handle),
+                        self.lib.qb_adjoint_workspace_bytes(self.handle))
         _check(self.lib.qb_plan_enable_adjoint(self.handle, _ptr(ws), ws.numel()), "qb_plan_enable_adjoint")
         self.ws_adj = ws
 
@@ -641,10 +651,10 @@ class Batch:
         self.lib = load()
         self.problems = list(problems)
         arr = (_Problem * len(self.problems))(*[p._c() for p in self.problems])
-        nbytes = self.lib.qb_batch_workspace_bytes(arr, len(self.problems))
-        if nbytes == 0:
+        least = self.lib.qb_batch_workspace_bytes(arr, len(self.problems))
+        if least == 0:
             _check(QB_EINVAL, "qb_batch_workspace_bytes")
-        self.ws = _workspace(nbytes)
+        self.ws = _workspace(self.lib.qb_batch_workspace_bytes_preferred(arr, len(self.problems)), least)
         h = ctypes.c_void_p()
         _check(self.lib.qb_batch_create(arr, len(self.problems), _ptr(self.ws), self.ws.numel(), ctypes.byref(h)),
                "qb_batch_create")

@@ -435,11 +435,11 @@ struct CollBufs {
 };
 
 // The buffers of C cells, I_3 in launches of I cells; with `one` (a single
-// summation group everywhere) the least that the pipeline runs in.
+// summation group everywhere) and I = C the least a plan takes.
 template <typename T>
 bool carve_collision(Arena& a, const qb_plan_s* pl, size_t C, size_t I, bool one, CollBufs& b) {
   const size_t FSZ = (size_t)pl->P * pl->P, J = pl->prob.J, t = sizeof(T);
-  const size_t ng = one ? 1 : max_node_groups(pl->prob), tg = one ? 1 : term_groups(pl->prob);
+  const size_t ng = node_groups(pl->prob, one), tg = term_groups(pl->prob.J, one);
   const size_t tasks = I * J * ng;
   return a.take(&b.i3s, tasks * qb::kI3sPlanes<T> * FSZ * t) && a.take(&b.spec, C * 8 * FSZ * t) &&
          a.take(&b.wP, C * 5 * FSZ * t) && a.take(&b.terms, C * qb::kTermPlanes * tg * FSZ * t) &&
@@ -464,7 +464,7 @@ bool build_buffers(qb_plan_s* pl) {
   const qb_problem& p = pl->prob;
   const size_t st = (size_t)4 * p.Nx * p.N * p.N * sizeof(T);
   CollBufs b;
-  if (!carve_collision<T>(pl->ws, pl, pl->wcells, pl->i3cells, false, b)) {
+  if (!carve_collision<T>(pl->ws, pl, pl->wcells, pl->i3cells, pl->one_group, b)) {
     set_error("plan workspace exhausted");
     return false;
   }
@@ -480,7 +480,7 @@ bool build_adjoint(qb_plan_s* pl) {
   void** states[] = {&pl->wn, &pl->wa, &pl->w1, &pl->wb, &pl->lb, &pl->ls, &pl->la, &pl->cg, &pl->g0};
   for (void** q : states)
     if (!pl->alloc_adj(q, st)) return false;
-  const size_t tg = term_groups(p), tasks = (size_t)pl->i3cells * J * max_node_groups(p);
+  const size_t tg = term_groups(p.J, pl->vjp_one), tasks = (size_t)pl->vjp_cells * J * node_groups(p, pl->vjp_one);
   return pl->alloc_adj(&pl->lamP, C * 4 * FSZ * b) && pl->alloc_adj(&pl->acot, C * 16 * FSZ * b) &&
          pl->alloc_adj(&pl->gspec, C * 22 * tg * FSZ * b) && pl->alloc_adj(&pl->gf0, C * 7 * tg * FSZ * b) &&
          pl->alloc_adj(&pl->i3g, tasks * 8 * FSZ * b) && pl->alloc_adj(&pl->i3sb, tasks * 4 * FSZ * b) &&
@@ -1063,14 +1063,18 @@ qb_status validate(const qb_problem* p) {
 }
 
 // Default number of cells one collision launch covers: the collision
-// workspace (about (43 + 12 J) P^2 scalars per cell) is sized for this many.
+// workspace is sized for this many.  In planes of P^2 scalars a cell takes
+// 46 + 12 J in float32 and 46 + 14 J in float64 with one summation group;
+// with groups 21 + 25 tg, and an I_3 task (ng J of them per cell of a
+// launch of k_i3) 14.
 constexpr int kChunkCells = 512;
 
 int chunk_cells(const qb_problem& p, int max_cells) {
   return std::min(p.Nx, max_cells > 0 ? max_cells : kChunkCells);
 }
 
-void init_plan(qb_plan_s* pl, const qb_problem& problem, int max_cells) {
+// `one`: a single summation group everywhere (float32 always)
+void init_plan(qb_plan_s* pl, const qb_problem& problem, int max_cells, bool one) {
   pl->prob = problem;
   pl->P = 2 * problem.N;
   pl->E = cfg_E(problem.precision, pl->P);
@@ -1078,7 +1082,8 @@ void init_plan(qb_plan_s* pl, const qb_problem& problem, int max_cells) {
   pl->TPR = pl->P / pl->E;
   pl->NT = pl->P * pl->TPR;
   pl->wcells = chunk_cells(problem, max_cells);
-  pl->i3cells = i3_launch_cells(problem, pl->wcells);
+  pl->one_group = one || !qb::groups_of(problem.precision);
+  pl->i3cells = i3_launch_cells(problem, pl->wcells, pl->one_group);
 }
 
 // Carve (and, unless measuring, fill) everything a plan holds: phases and
@@ -1094,16 +1099,44 @@ bool layout_any(qb_plan_s* pl) {
   return pl->prob.precision == QB_F64 ? layout_plan<double>(pl) : layout_plan<float>(pl);
 }
 
-size_t plan_workspace_bytes(const qb_problem& problem, int max_cells) {
+// Workspace of a plan with k_i3 in launches of `i3cells` cells (0: as many as
+// i3_launch_cells).
+size_t plan_workspace_bytes(const qb_problem& problem, int max_cells, bool one, int i3cells = 0) {
   qb_plan_s pl;
-  init_plan(&pl, problem, max_cells);
+  init_plan(&pl, problem, max_cells, one);
+  if (i3cells > 0) pl.i3cells = i3cells;
   pl.ws.reset(nullptr, 0, true);
   return layout_any(&pl) ? pl.ws.used : 0;
 }
 
+// Largest n in 1 .. most with bytes(n) <= cap (0 if there is none), bytes growing with n.
+template <typename F>
+int most_that_fit(int most, size_t cap, F bytes) {
+  int lo = 0, hi = most;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) / 2;
+    if (bytes(mid) <= cap)
+      lo = mid;
+    else
+      hi = mid - 1;
+  }
+  return lo;
+}
+
+// A plan for a workspace of `bytes` that holds at least the one-group layout:
+// with the summation groups if there is room for one cell's, k_i3 then in
+// launches of as many cells as fit.
+void init_plan_in(qb_plan_s* pl, const qb_problem& problem, int max_cells, size_t bytes) {
+  init_plan(pl, problem, max_cells, false);
+  if (pl->one_group) return;
+  pl->i3cells = most_that_fit(pl->i3cells, bytes,
+                              [&](int n) { return plan_workspace_bytes(problem, max_cells, false, n); });
+  if (pl->i3cells == 0) init_plan(pl, problem, max_cells, true);
+}
+
 qb_plan_s* create_plan(const qb_problem& problem, int max_cells, void* ws, size_t ws_bytes) {
   qb_plan_s* pl = new qb_plan_s();
-  init_plan(pl, problem, max_cells);
+  init_plan_in(pl, problem, max_cells, ws_bytes);
   pl->ws.reset(ws, ws_bytes, false);
   if (!layout_any(pl)) {
     delete pl;
@@ -1112,13 +1145,28 @@ qb_plan_s* create_plan(const qb_problem& problem, int max_cells, void* ws, size_
   return pl;
 }
 
-size_t adjoint_workspace_bytes(qb_plan_s* pl) {
-  const Arena keep = pl->adj;
-  pl->adj.reset(nullptr, 0, true);
-  const bool ok = pl->prob.precision == QB_F64 ? build_adjoint<double>(pl) : build_adjoint<float>(pl);
-  const size_t n = pl->adj.used;
-  pl->adj = keep;
-  return ok ? n : 0;
+// Reverse-mode workspace with I_3 in launches of `cells` cells, in groups or
+// with one (then of as many cells as the plan's own I_3 buffers hold).
+void set_vjp_groups(qb_plan_s* pl, bool one, int cells = 0) {
+  pl->vjp_one = one;
+  pl->vjp_cells = one ? (int)std::min<int64_t>(pl->wcells, (int64_t)pl->i3cells * node_groups(pl->prob, pl->one_group))
+                      : cells;
+}
+
+bool layout_adjoint(qb_plan_s* pl) {
+  return pl->prob.precision == QB_F64 ? build_adjoint<double>(pl) : build_adjoint<float>(pl);
+}
+
+size_t adjoint_workspace_bytes(const qb_plan_s* plan, bool one, int cells = 0) {
+  qb_plan_s pl;  // the layout alone: a plan that holds no events
+  pl.prob = plan->prob;
+  pl.P = plan->P;
+  pl.wcells = plan->wcells;
+  pl.i3cells = plan->i3cells;
+  pl.one_group = plan->one_group;
+  set_vjp_groups(&pl, one || pl.one_group, cells > 0 ? cells : pl.i3cells);
+  pl.adj.reset(nullptr, 0, true);
+  return layout_adjoint(&pl) ? pl.adj.used : 0;
 }
 
 }  // namespace
@@ -1256,13 +1304,18 @@ qb_problem group_problem(const qb_batch_s* b, const qb_batch_s::Group& g) {
 
 // Lay out every group in [ws, ws + ws_bytes) (measuring when ws is null):
 // group k's plan workspace starts at a 256-byte boundary after group k-1's.
-qb_status batch_layout(qb_batch_s* b, void* ws, size_t ws_bytes) {
+// Not `preferred`: every plan within the size of its one-group layout.
+qb_status batch_layout(qb_batch_s* b, bool preferred, void* ws, size_t ws_bytes) {
   const bool measure = ws == nullptr;
   size_t off = 0;
   for (qb_batch_s::Group& g : b->groups) {
     off = (off + 255) & ~(size_t)255;
     qb_plan_s* pl = new qb_plan_s();
-    init_plan(pl, group_problem(b, g), 0);
+    const qb_problem gp = group_problem(b, g);
+    if (preferred)
+      init_plan(pl, gp, 0, false);
+    else
+      init_plan_in(pl, gp, 0, plan_workspace_bytes(gp, 0, true));
     pl->ws.reset(measure ? nullptr : (char*)ws + off, measure ? 0 : (off < ws_bytes ? ws_bytes - off : 0), measure);
     g.plan = pl;
     const bool ok = b->precision == QB_F64 ? group_layout<double>(b, g) : group_layout<float>(b, g);
@@ -1271,6 +1324,15 @@ qb_status batch_layout(qb_batch_s* b, void* ws, size_t ws_bytes) {
   }
   b->ws_used = off;
   return QB_OK;
+}
+
+qb_status batch_groups(const qb_problem* problems, int nprob, qb_batch_s* b);
+
+size_t batch_workspace_bytes(const qb_problem* problems, int nprob, bool preferred) {
+  if (!problems || nprob < 1) return 0;
+  qb_batch_s b;
+  if (batch_groups(problems, nprob, &b) != QB_OK || batch_layout(&b, preferred, nullptr, 0) != QB_OK) return 0;
+  return b.ws_used;
 }
 
 // Validate a batch description and group its problems by N.
@@ -1388,6 +1450,7 @@ qb_status do_collision_static(qb_plan_s* pl, void* base, const void* W, void* C,
   }
   const CollBufs keep = get_bufs(pl);
   const int keep_nx = pl->prob.Nx, keep_wc = pl->wcells, keep_ic = pl->i3cells;
+  const bool keep_one = pl->one_group;
   set_bufs(pl, b);
   pl->one_group = true;  // as many cells as fit
   bool ok = true;
@@ -1408,7 +1471,7 @@ qb_status do_collision_static(qb_plan_s* pl, void* base, const void* W, void* C,
     }
   }
   set_bufs(pl, keep);
-  pl->one_group = false;
+  pl->one_group = keep_one;
   pl->prob.Nx = keep_nx;
   pl->wcells = keep_wc;
   pl->i3cells = keep_ic;
@@ -1422,7 +1485,12 @@ extern "C" {
 
 size_t qb_workspace_bytes(const qb_problem* problem, int32_t max_cells) {
   if (validate(problem) != QB_OK || max_cells < 0) return 0;
-  return plan_workspace_bytes(*problem, max_cells);
+  return plan_workspace_bytes(*problem, max_cells, true);
+}
+
+size_t qb_workspace_bytes_preferred(const qb_problem* problem, int32_t max_cells) {
+  if (validate(problem) != QB_OK || max_cells < 0) return 0;
+  return std::max(plan_workspace_bytes(*problem, max_cells, true), plan_workspace_bytes(*problem, max_cells, false));
 }
 
 qb_status qb_plan_create(const qb_problem* problem, int32_t max_cells, void* workspace, size_t ws_bytes,
@@ -1432,7 +1500,7 @@ qb_status qb_plan_create(const qb_problem* problem, int32_t max_cells, void* wor
   qb_status st = validate(problem);
   if (st != QB_OK) return st;
   if (max_cells < 0 || !workspace) return QB_EINVAL;
-  if (ws_bytes < plan_workspace_bytes(*problem, max_cells)) return QB_EWORKSPACE;
+  if (ws_bytes < plan_workspace_bytes(*problem, max_cells, true)) return QB_EWORKSPACE;
   qb_plan_s* pl = create_plan(*problem, max_cells, workspace, ws_bytes);
   if (!pl) return QB_EHIP;
   // set-up of qb_collision_static on this device
@@ -1520,16 +1588,23 @@ qb_status qb_step_fluxes(qb_plan plan, void* W, const double* B, double dt, int3
   return do_step<float>(plan, W, B, dt, nsteps, moments_out, nullptr, s, inflow);
 }
 
-size_t qb_adjoint_workspace_bytes(qb_plan plan) { return plan ? adjoint_workspace_bytes(plan) : 0; }
+size_t qb_adjoint_workspace_bytes(qb_plan plan) { return plan ? adjoint_workspace_bytes(plan, true) : 0; }
+
+size_t qb_adjoint_workspace_bytes_preferred(qb_plan plan) {
+  return plan ? std::max(adjoint_workspace_bytes(plan, true), adjoint_workspace_bytes(plan, false)) : 0;
+}
 
 qb_status qb_plan_enable_adjoint(qb_plan plan, void* workspace, size_t ws_bytes) {
   if (!plan) return QB_EINVAL;
   if (plan->adjoint) return QB_OK;
   if (!workspace) return QB_EINVAL;
-  if (ws_bytes < adjoint_workspace_bytes(plan)) return QB_EWORKSPACE;
+  if (ws_bytes < adjoint_workspace_bytes(plan, true)) return QB_EWORKSPACE;
+  const int cells = plan->one_group ? 0 : most_that_fit(plan->i3cells, ws_bytes, [&](int n) {
+    return adjoint_workspace_bytes(plan, false, n);
+  });
+  set_vjp_groups(plan, cells == 0, cells);
   plan->adj.reset(workspace, ws_bytes, false);
-  const bool ok = plan->prob.precision == QB_F64 ? build_adjoint<double>(plan) : build_adjoint<float>(plan);
-  if (!ok) return QB_EWORKSPACE;
+  if (!layout_adjoint(plan)) return QB_EWORKSPACE;
   plan->adjoint = true;
   return QB_OK;
 }
@@ -1734,10 +1809,11 @@ qb_status qb_plan_tune(qb_plan plan, int32_t ncells, int32_t* tile, void* stream
 }
 
 size_t qb_batch_workspace_bytes(const qb_problem* problems, int32_t nprob) {
-  if (!problems || nprob < 1) return 0;
-  qb_batch_s b;
-  if (batch_groups(problems, nprob, &b) != QB_OK || batch_layout(&b, nullptr, 0) != QB_OK) return 0;
-  return b.ws_used;
+  return batch_workspace_bytes(problems, nprob, false);
+}
+
+size_t qb_batch_workspace_bytes_preferred(const qb_problem* problems, int32_t nprob) {
+  return std::max(batch_workspace_bytes(problems, nprob, true), batch_workspace_bytes(problems, nprob, false));
 }
 
 qb_status qb_batch_create(const qb_problem* problems, int32_t nprob, void* workspace, size_t ws_bytes,
@@ -1748,7 +1824,8 @@ qb_status qb_batch_create(const qb_problem* problems, int32_t nprob, void* works
   qb_status st = batch_groups(problems, nprob, b);
   if (st == QB_OK && !workspace) st = QB_EINVAL;
   if (st == QB_OK && ws_bytes < qb_batch_workspace_bytes(problems, nprob)) st = QB_EWORKSPACE;
-  if (st == QB_OK) st = batch_layout(b, workspace, ws_bytes);
+  if (st == QB_OK)
+    st = batch_layout(b, ws_bytes >= qb_batch_workspace_bytes_preferred(problems, nprob), workspace, ws_bytes);
   if (st == QB_OK && !hip_ok(hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking), "hipStreamCreate"))
     st = QB_EHIP;
   if (st != QB_OK) {

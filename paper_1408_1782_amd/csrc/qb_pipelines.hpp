@@ -61,7 +61,9 @@ bool collision_vjp_pipeline(qb_plan_s* pl, const T* w, const T* lam, T* out, int
                             hipStream_t s) {
   constexpr int NT = qb::Fft2<T, P, E>::NT;
   DevPlan<T> d = devplan<T>(pl, pl->vjp_tab);
-  node_groups((d.M + 1) / 2, !qb::grouped<T>, d.gs, d.ng);  // the reverse kernel always pairs its nodes
+  node_groups(d.M, true, pl->vjp_one, d.gs, d.ng);  // the reverse kernel always pairs its nodes
+  d.tg = term_groups(d.J, pl->vjp_one);
+  d.td = pl->vjp_one ? d.J : kTermDirs;
   int id = pl->begin(QB_K_DFT_IN, s);
   if constexpr (qb::grouped<T>)
     hipLaunchKernelGGL((qb::k_dft_in<T, P, E>), dim3(4 * ncells), dim3(NT), 0, s, d, w, cell0);
@@ -76,8 +78,8 @@ bool collision_vjp_pipeline(qb_plan_s* pl, const T* w, const T* lam, T* out, int
   hipLaunchKernelGGL((qb::k_terms_vjp<T, P, E>), dim3(ncells * qb::kTermsVjpTasks * d.tg), dim3(NT), 0, s, d);
   hipLaunchKernelGGL((qb::k_assemble_vjp<T>), dim3(blocks(nel, 256)), dim3(256), 0, s, d, ncells, P * P, 1);
   pl->end(id, s);
-  for (int c0 = 0; c0 < ncells; c0 += pl->i3cells) {
-    const int nc = std::min(pl->i3cells, ncells - c0);
+  for (int c0 = 0; c0 < ncells; c0 += pl->vjp_cells) {
+    const int nc = std::min(pl->vjp_cells, ncells - c0);
     const size_t F = (size_t)c0 * P * P;
     DevPlan<T> dc = d;
     dc.spec += 8 * F, dc.wP += 5 * F, dc.acot += 16 * F, dc.lamh += 4 * F, dc.gsum += 8 * F;

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstdint>
 #include <string>
 #include <vector>
 
@@ -56,7 +57,10 @@ struct qb_plan_s {
   int P, E, NT, TPR;
   int wcells;  // cells per collision launch (the workspace holds this many)
   int i3cells;  // cells per launch of k_i3 (its buffers hold this many)
-  bool one_group = false;  // one summation group each in k_i3 and k_terms (the least workspace)
+  bool one_group = false;  // one summation group each in k_i3 and k_terms: float32, and float64 in
+                           // a workspace too small for the groups
+  int vjp_cells = 0;       // the same of the reverse-mode pipeline
+  bool vjp_one = false;
   bool i3_pair = true;  // I_3 kernel pairs the Gauss-Legendre nodes (tuned; default per tile)
   int vjp_variant = 0;  // I_3 adjoint: 0 row w_bar in memory, 1 in registers (cfg_vjp; tuned)
   int vjp_E = 0;        // tile shape of the reverse-mode pipeline (cfg_vjp; tuned; 0: the forward tile)
@@ -140,32 +144,44 @@ struct qb_plan_s {
   }
 };
 
-// Summation groups of the I_3 nodes (pairs of nodes when paired; see k_i3):
-// 4 nodes to a group, 2 or 3 where there are too few for 4 groups.
-inline void node_groups(int nnode, bool one, int& gs, int& ng) {
-  gs = one ? nnode : std::min(4, std::max(2, (nnode + 3) / 4));
-  ng = (nnode + gs - 1) / gs;
+// Summation groups of the I_3 nodes (see k_i3): 4 pairs of nodes to a group,
+// 2 or 3 where there are too few for 4 groups.  Unpaired, a group holds as
+// many nodes (2 gs), so that both kernels run in the same buffers.
+inline void node_groups(int M, bool paired, bool one, int& gs, int& ng) {
+  const int npair = (M + 1) / 2;
+  gs = one ? npair : std::min(4, std::max(2, (npair + 3) / 4));
+  ng = (npair + gs - 1) / gs;
+  if (!paired) gs *= 2;
 }
-inline int max_node_groups(const qb_problem& p) {
-  if (!qb::groups_of(p.precision)) return 1;
-  int gs, a, b;
-  node_groups((p.M + 1) / 2, false, gs, a);
-  node_groups(p.M, false, gs, b);
-  return std::max(a, b);
+inline int node_groups(const qb_problem& p, bool one) {
+  int gs, ng;
+  node_groups(p.M, true, one, gs, ng);
+  return ng;
 }
 // Directions per group of k_terms: 4 pairs, 8 transforms beside the final one.
 constexpr int kTermDirs = 8;
 inline int term_groups(int J, bool one) { return one ? 1 : (J + kTermDirs - 1) / kTermDirs; }
-inline int term_groups(const qb_problem& p) { return term_groups(p.J, !qb::groups_of(p.precision)); }
 
-// Cells per launch of k_i3 in chunks of wcells cells: enough tasks for the
-// partly empty last round of a launch not to matter (some 30 rounds of the
-// resident workgroups), and no more I_3 buffers than `wcells` cells with one
-// task per (cell, j) would take beyond that.
-inline int i3_launch_cells(const qb_problem& p, int wcells) {
-  const int ng = max_node_groups(p);
-  const int tasks = p.N == 16 ? 65536 : p.N == 32 ? 32768 : 16384;
-  return std::min(wcells, std::max((wcells + ng - 1) / ng, tasks / (p.J * ng)));
+// Cells per launch of k_i3 in chunks of wcells cells.  At most as many as the
+// I_3 buffers of one task per (cell, j) would hold, or 3.8 GB of them: a plan
+// of many cells then takes little more than with one group (+15 % at J = 32),
+// where all cells in one launch would take ng times as much.  Up to that, the
+// number that leaves the fewest rounds of resident workgroups partly empty
+// over the launches: 60 cells at N = 32, J = 36, M = 48 take 17.2 ms in one
+// launch, 18.5 in launches of 18 cells (15.2 rounds each).
+inline int i3_launch_cells(const qb_problem& p, int wcells, bool one) {
+  const int ng = node_groups(p, one), per_cell = p.J * ng;
+  const int tasks = p.N == 16 ? 32768 : p.N == 32 ? 8192 : 2048;
+  const int most = std::min(wcells, std::max({1, (wcells + ng - 1) / ng, tasks / per_cell}));
+  const int resident = p.N == 16 ? 1024 : 256;  // workgroups of the starting tile on the card
+  auto rounds = [&](int cells) { return (int64_t)(cells * per_cell + resident - 1) / resident; };
+  int best = most;
+  int64_t least = INT64_MAX;
+  for (int n = most; n >= (most + 1) / 2; --n) {
+    const int64_t r = wcells / n * rounds(n) + rounds(wcells % n);
+    if (r < least) least = r, best = n;
+  }
+  return best;
 }
 
 // Device view of the plan with the table set `tab` (the forward pipeline
@@ -202,10 +218,9 @@ inline DevPlan<T> devplan(qb_plan_s* pl, int tab) {
   d.i3sum = (T*)pl->i3sum;
   d.i3p = (T*)pl->i3p;
   d.i3ps = (T*)pl->i3ps;
-  const bool one = pl->one_group || !qb::groups_of(pl->prob.precision);
-  node_groups(pl->i3_pair ? (d.M + 1) / 2 : d.M, one, d.gs, d.ng);
-  d.tg = term_groups(d.J, one);
-  d.td = one ? d.J : kTermDirs;
+  node_groups(d.M, pl->i3_pair, pl->one_group, d.gs, d.ng);
+  d.tg = term_groups(d.J, pl->one_group);
+  d.td = pl->one_group ? d.J : kTermDirs;
   d.lamP = (T*)pl->lamP;
   d.acot = (T*)pl->acot;
   d.gspec = (T*)pl->gspec;
