@@ -289,8 +289,9 @@ qb_status qb_diagnostics(qb_plan plan, const void* W, const void* C, const qb_fd
  * 16, and 8 at P = 32 in float64.
  * ------------------------------------------------------------------------- */
 
-/* Use tile shape E on this plan (QB_ENOTSUP if not compiled for its P).
- * Synchronous the first time a shape is used (builds its tables). */
+/* Use tile shape E on this plan (QB_ENOTSUP if not compiled for its P), in
+ * the reverse mode too unless qb_plan_set_adjoint_tile or the tuner gave that
+ * a tile of its own.  Synchronous the first time a shape is used (builds its tables). */
 qb_status qb_plan_set_tile(qb_plan plan, int32_t E);
 
 /* Autotuner: time the collision pipeline on the plan's first `ncells` cells
@@ -312,8 +313,10 @@ qb_status qb_plan_set_pairing(qb_plan plan, int32_t paired);
 
 /* Tile shape E of the reverse-mode pipeline (qb_collision_vjp and the
  * collision adjoints of qb_adjoint_step), independent of the forward tile;
- * 0 follows the forward tile.  A plan starts with the shape measured fastest
- * (8 at P = 32 and 64 in float64, else 16).  QB_ENOTSUP if E is not compiled
+ * 0 follows the forward tile, as it does after a qb_plan_set_tile.  Until one
+ * of these calls or the tuner, a plan runs the shape and I_3 adjoint kernel
+ * measured fastest (8 and 1 at P = 32 and 64 in float64, else 16 and 0); a
+ * tile set here runs kernel 0 unless one was chosen.  QB_ENOTSUP if E is not compiled
  * for the plan's padded grid.  Synchronous the first time a shape
  * is used (fills its tables). */
 qb_status qb_plan_set_adjoint_tile(qb_plan plan, int32_t E);

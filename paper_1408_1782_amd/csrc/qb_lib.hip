@@ -1037,6 +1037,7 @@ qb_status do_tune(qb_plan_s* pl, int ncells, int* chosen, hipStream_t s) {
     }
     if (!select_vjp_tile<T>(pl, vE)) return QB_EHIP;
     pl->vjp_variant = vv;
+    pl->vjp_tile_set = pl->vjp_variant_set = true;
   }
   return QB_OK;
 }
@@ -1740,7 +1741,14 @@ qb_status qb_plan_set_tile(qb_plan plan, int32_t E) {
   const std::vector<int> c = tile_candidates(plan->P);
   if (std::find(c.begin(), c.end(), (int)E) == c.end()) return QB_ENOTSUP;
   const bool ok = plan->prob.precision == QB_F64 ? select_tile<double>(plan, E) : select_tile<float>(plan, E);
-  return ok ? QB_OK : QB_EHIP;
+  if (!ok) return QB_EHIP;
+  // the reverse mode leaves its starting tile and follows this one
+  if (!plan->vjp_tile_set) {
+    plan->vjp_E = 0;
+    plan->vjp_tab = plan->cur_tab;
+    if (!plan->vjp_variant_set) plan->vjp_variant = 0;
+  }
+  return QB_OK;
 }
 
 qb_status qb_plan_set_scheme(qb_plan plan, int32_t limiter, int32_t field) {
@@ -1771,7 +1779,10 @@ qb_status qb_plan_set_adjoint_tile(qb_plan plan, int32_t E) {
     if (std::find(c.begin(), c.end(), (int)E) == c.end()) return QB_ENOTSUP;
   }
   const bool ok = plan->prob.precision == QB_F64 ? select_vjp_tile<double>(plan, E) : select_vjp_tile<float>(plan, E);
-  return ok ? QB_OK : QB_EHIP;
+  if (!ok) return QB_EHIP;
+  plan->vjp_tile_set = true;
+  if (!plan->vjp_variant_set) plan->vjp_variant = 0;
+  return QB_OK;
 }
 
 qb_status qb_plan_set_persistent(qb_plan plan, int32_t persistent) {
@@ -1783,6 +1794,7 @@ qb_status qb_plan_set_persistent(qb_plan plan, int32_t persistent) {
 qb_status qb_plan_set_adjoint_variant(qb_plan plan, int32_t variant) {
   if (!plan || variant < 0 || variant > 1) return QB_EINVAL;
   plan->vjp_variant = variant;
+  plan->vjp_variant_set = true;
   return QB_OK;
 }
 

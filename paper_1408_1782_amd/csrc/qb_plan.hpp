@@ -65,6 +65,7 @@ struct qb_plan_s {
   int vjp_variant = 0;  // I_3 adjoint: 0 row w_bar in memory, 1 in registers (cfg_vjp; tuned)
   int vjp_E = 0;        // tile shape of the reverse-mode pipeline (cfg_vjp; tuned; 0: the forward tile)
   int vjp_tab = 0;      // its table set
+  bool vjp_tile_set = false, vjp_variant_set = false;  // chosen by the caller or the tuner, not by cfg_vjp
   int term_sel = 3;     // collision terms assembled: 1 C_c, 2 C_d, 3 both
   int limiter = 0;      // transport slope limiter: 0 minmod, 1 superbee, 2 MC, 3 van Leer
   int field_mode = 0;   // field term: 0 inside the Heun step, 1 exact rotation split around it
