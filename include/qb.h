@@ -453,12 +453,13 @@ qb_status qb_adjoint_step(qb_plan plan, const void* W, const void* record, const
  * bracketed by a pair of HIP events on its stream; qb_profile_read
  * synchronizes those events and returns, for one kernel class, the summed
  * duration in milliseconds and the number of launches since the last read
- * (then resets that class).  Profiling adds two event records per launch. */
+ * (then resets that class); I_3 and its transpose count once per collision
+ * launch, also where their buffers cut it into several.  Profiling adds two
+ * event records per launch. */
 typedef enum {
   QB_K_DFT_IN = 0,  /* velocity grid -> Fourier coefficients, padded-grid interpolants */
   QB_K_TERMS = 1,   /* I_1 (kernel G), I_4 and I_2 (kernel H_J) */
-  QB_K_I3 = 2,      /* I_3 (kernel H_JM) and the sums of its partials, the dominant work;
-                       counted once per collision launch */
+  QB_K_I3 = 2,      /* I_3 (kernel H_JM), the dominant kernel */
   QB_K_COMBINE = 3, /* Pauli assembly, final transform, output on the grid */
   QB_K_TRANSPORT = 4,
   QB_K_HEUN = 5,

@@ -1726,7 +1726,7 @@ qb_status qb_profile_read(qb_plan plan, int32_t kernel, double* total_ms, int64_
     float e = 0.f;
     if (!hip_ok(hipEventElapsedTime(&e, r.a, r.b), "hipEventElapsedTime")) return QB_EHIP;
     ms += e;
-    ++n;
+    n += r.counts;
     plan->pool.push_back(r.a);
     plan->pool.push_back(r.b);
   }

@@ -26,7 +26,6 @@ bool collision_pipeline(qb_plan_s* pl, const T* w, T* c, int ncells, int cell0, 
                      ncells);
   pl->end(id, s);
   // I_3 and its sums in launches of at most i3cells cells (their buffers)
-  id = pl->begin(QB_K_I3, s);
   for (int c0 = 0; c0 < ncells; c0 += pl->i3cells) {
     const int nc = std::min(pl->i3cells, ncells - c0);
     DevPlan<T> dc = d;
@@ -36,19 +35,20 @@ bool collision_pipeline(qb_plan_s* pl, const T* w, T* c, int ncells, int cell0, 
     dc.i3sum += (size_t)c0 * 4 * P * P;
     dc.i3ps += (size_t)c0 * 4 * P * P;
     const int ntask = nc * d.J * d.ng;
+    id = pl->begin(QB_K_I3, s, c0 == 0);
     if (pl->i3_pair)
       hipLaunchKernelGGL((qb::k_i3<T, P, E, true>), dim3(grid(ntask, (const void*)qb::k_i3<T, P, E, true>)), dim3(NT),
                          0, s, dc, nc);
     else
       hipLaunchKernelGGL((qb::k_i3<T, P, E, false>), dim3(grid(ntask, (const void*)qb::k_i3<T, P, E, false>)),
                          dim3(NT), 0, s, dc, nc);
+    pl->end(id, s);
     if constexpr (qb::grouped<T>)
       hipLaunchKernelGGL((qb::k_assemble<T, P, E>), dim3(nc * (P * P / qb::kAsmEl<T>)), dim3(32 * qb::kAsmRow), 0, s,
                          dc, nc);
     else
       hipLaunchKernelGGL((qb::k_assemble_seq<T, P, E>), dim3(blocks((size_t)nc * P * P, 256)), dim3(256), 0, s, dc, nc);
   }
-  pl->end(id, s);
   id = pl->begin(QB_K_COMBINE, s);
   hipLaunchKernelGGL((qb::k_combine<T, P, E>), dim3(2 * ncells), dim3(NT), 0, s, d, c, cell0);
   pl->end(id, s);
@@ -84,17 +84,17 @@ bool collision_vjp_pipeline(qb_plan_s* pl, const T* w, const T* lam, T* out, int
     DevPlan<T> dc = d;
     dc.spec += 8 * F, dc.wP += 5 * F, dc.acot += 16 * F, dc.lamh += 4 * F, dc.gsum += 8 * F;
     dc.gf0 += 7 * d.tg * F, dc.gspec += 22 * d.tg * F;
-    id = pl->begin(QB_K_I3_ADJOINT, s);
+    id = pl->begin(QB_K_I3_ADJOINT, s, c0 == 0);
     if (pl->vjp_variant == 1)
       hipLaunchKernelGGL((qb::k_i3_vjp_reg<T, P, E, true>), dim3(nc * d.J * d.ng), dim3(NT), 0, s, dc, nc);
     else
       hipLaunchKernelGGL((qb::k_i3_vjp_reg<T, P, E, false>), dim3(nc * d.J * d.ng), dim3(NT), 0, s, dc, nc);
     pl->end(id, s);
-    id = pl->begin(QB_K_ADJOINT, s);
+    id = pl->begin(QB_K_ADJOINT, s, c0 == 0);
     hipLaunchKernelGGL((qb::k_grad_pre<T>), dim3(blocks((size_t)nc * P * P * 8, 256)), dim3(256), 0, s, dc, nc, P * P);
     pl->end(id, s);
   }
-  id = pl->begin(QB_K_ADJOINT, s);
+  id = pl->begin(QB_K_ADJOINT, s, false);
   hipLaunchKernelGGL((qb::k_grad_out<T, P, E>), dim3(2 * ncells), dim3(NT), 0, s, d, out, cell0);
   pl->end(id, s);
   return hip_ok(hipGetLastError(), "collision adjoint launch");

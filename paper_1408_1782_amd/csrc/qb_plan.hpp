@@ -98,6 +98,7 @@ struct qb_plan_s {
   struct Rec {
     int kernel;
     hipEvent_t a, b;
+    bool counts;
   };
   std::vector<Rec> recs;
   std::vector<hipEvent_t> pool;
@@ -132,10 +133,11 @@ struct qb_plan_s {
     (void)hipEventCreate(&e);
     return e;
   }
-  // bracket one launch: call begin() before and end() after the launch
-  int begin(int kernel, hipStream_t s) {
+  // bracket one launch: call begin() before and end() after the launch; not
+  // `counts`: more of a launch that has been counted
+  int begin(int kernel, hipStream_t s, bool counts = true) {
     if (!profiling) return -1;
-    Rec r{kernel, event(), event()};
+    Rec r{kernel, event(), event(), counts};
     (void)hipEventRecord(r.a, s);
     recs.push_back(r);
     return (int)recs.size() - 1;
