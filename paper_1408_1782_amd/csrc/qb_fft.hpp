@@ -248,6 +248,13 @@ __device__ __forceinline__ void add_lanes(double (&z)[E], double s) {
 }
 
 // ------------------------------------------------------------------ engine
+// Whether the spectra carry the lane signs of lanes_fwd; the host's table of
+// -k (negk, for k_grad_pre) has to agree.
+template <typename T>
+constexpr bool signed_spectra(int P) {
+  return !(sizeof(T) == 4 && P == 128);
+}
+
 template <typename T, int P_, int E_, bool XB_ = false>
 struct Fft2 {
   static constexpr int P = P_;
@@ -270,8 +277,7 @@ struct Fft2 {
   static_assert(E * TPR == P, "E * TPR must equal P");
   static_assert(P % BW == 0, "P must be a multiple of the bank width");
 
-  // whether the spectra carry the lane signs of lanes_fwd
-  static constexpr bool SIGNED = !(sizeof(T) == 4 && P == 128);
+  static constexpr bool SIGNED = signed_spectra<T>(P);
 
   int t, line, q, bq;
   T* lds;          // transpose buffer, LDS_SCALARS scalars

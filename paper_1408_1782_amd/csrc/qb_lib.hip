@@ -234,12 +234,11 @@ bool fill_layout_tables(qb_plan_s* pl, qb_plan_s::TabSet& ts, const NaturalTable
     auto ones = [&](int k) { const int q = qb::bitrev_rt(k / E, lb); return (q ^ (q >> 1)) & 1; };
     return ones(kx) ^ ones(ky);
   };
-  const bool with_signs = !(sizeof(T) == 4 && P == 128);  // Fft2::SIGNED
   std::vector<unsigned> negk(FSZ);
   for (int kx = 0; kx < P; ++kx)
     for (int ky = 0; ky < P; ++ky) {
       const int nx = (P - kx) % P, ny = (P - ky) % P;
-      const unsigned flip = with_signs && sign(kx, ky) != sign(nx, ny) ? 0x80000000u : 0u;
+      const unsigned flip = qb::signed_spectra<T>(P) && sign(kx, ky) != sign(nx, ny) ? 0x80000000u : 0u;
       negk[pos[(size_t)kx * P + ky]] = (unsigned)pos[(size_t)nx * P + ny] | flip;
     }
   ts.built = put<T>(ts.tw, tw) && table(ts.phip, t.phip, 1.0) && table(ts.Kt, t.Kt, invP2) &&

@@ -15,6 +15,9 @@
 
 using qb::DevPlan;
 
+static_assert(qb::groups_of(QB_F64) == qb::grouped<double> && qb::groups_of(QB_F32) == qb::grouped<float>,
+              "host and device agree on which precision sums in groups");
+
 // Records the text of a failed HIP call for qb_last_error(); true on success.
 bool hip_ok(hipError_t e, const char* what);
 // Records a message for qb_last_error().
