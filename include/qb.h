@@ -325,8 +325,8 @@ qb_status qb_plan_set_adjoint_tile(qb_plan plan, int32_t E);
 qb_status qb_plan_set_adjoint_variant(qb_plan plan, int32_t variant);
 
 /* Launch shape of the two heavy collision kernels (I_1 / I_2 / I_4 and
- * I_3): 0 (the default) launches one workgroup per task, (cell, term) or
- * (cell, j); 1 launches a persistent grid of as many workgroups as are
+ * I_3): 0 (the default) launches one workgroup per task, (cell, term, group
+ * of directions) or (cell, j, group of nodes); 1 launches a persistent grid of as many workgroups as are
  * resident at once on the device (a multiple of 8), each striding over the
  * task list.  Both compute the same values bit for bit; qb_plan_tune picks
  * the faster.  For a batch the task list spans every problem of a grid size. */

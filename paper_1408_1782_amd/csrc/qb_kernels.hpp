@@ -26,8 +26,14 @@ struct Cfg {
 // Float64 sums run in groups, one workgroup each (k_i3, k_terms and their
 // transposes).  A float32 plan keeps one chain per (cell, j) and per (cell,
 // task), in the order of the nodes and directions, and the transforms of the
-// input stage packed in pairs: its results are compared across versions
-// through float64 moments, which resolve the rounding of the float32 sums.
+// input stage packed in pairs, so that its results stay the numbers they were
+// before there were groups: float64 moments resolve the rounding of float32
+// sums.  (Not so the reverse mode at P = 128: in k_terms_vjp the compiler now
+// orders the operands of some a b + c d the other way round, so the other
+// product is the one rounded before the fused multiply-add.  The gradient's
+// error against float64 is as before, 2.7e-7 rms in eight collisions.)
+// The price is long tasks: a step of 40 cells at N = 32 between walls takes
+// 7.5 ms, about the same as before.
 constexpr bool groups_of(int precision) { return precision == 0; }  // QB_F64
 template <typename T>
 constexpr bool grouped = sizeof(T) == 8;
@@ -232,21 +238,19 @@ __global__ void k_state_to_api(const T* __restrict__ w, TA* __restrict__ W, int 
 }
 
 // ------------------------------------------------------------------ engine setup
-// Whether the LDS of a compute unit holds two planes of the transpose buffer
-// (all at P <= 64).
-template <typename T, int P, int E>
+// Both planes of a transpose at once outside the I_3 kernels (which decide by
+// I3Regs::XB): at P = 64 in float64 they take at most 73 KB, and two workgroups
+// share a compute unit; at P = 128 one plane takes 68 (float32) or 136 KB.
+template <int P>
 constexpr bool two_planes = P <= 64;
 
-template <typename T, int P, int E, bool XB = two_planes<T, P, E>>
+template <typename T, int P, int E, bool XB = two_planes<P>>
 struct Kern {
   using Eng = Fft2<T, P, E, XB>;
   static constexpr int NT = Eng::NT;
   static constexpr int TPR = Eng::TPR;
   static constexpr int FSZ = P * P;
   static constexpr int LDS = Eng::LDS_SCALARS + Eng::TW_SCALARS;
-  // least occupancy of k_i3 (waves per SIMD): two workgroups of 256 threads
-  // per compute unit, which a few registers more than 256 would halve
-  static constexpr int WAVES = 1;
 };
 
 template <typename T, int P, int E, bool XB>
@@ -296,11 +300,11 @@ struct I3Regs {
     return PR && !sreg<PR>() && P == 128 && sizeof(T) == 4 &&
            (LDS_SCALARS + P * P) * (int)sizeof(T) <= 160 * 1024;
   }
-  // At P = 64 with E = 16 (256 threads) the register plan leaves two
-  // workgroups per compute unit, each with half of the 160 KB of LDS: the
-  // output accumulators that fit beside the transpose buffer stay in LDS for
-  // the whole node loop (3 in float32, 1 in float64) instead of going
-  // through memory at every node.
+  // Output accumulators that stay in LDS beside the transpose buffer for the
+  // whole node loop at P = 64, instead of going through memory at every node.
+  // Two workgroups share the 160 KB of a compute unit, but for float64 with
+  // 512 threads, which has it alone: 3 at E = 16 and 2 at E = 8 in float32,
+  // none at E = 16 (two planes fill its half) and 2 at E = 8 in float64.
   template <bool PR, int LDS_SCALARS>
   static constexpr int lds_acc() {
     if (!PR || P != 64 || NT < 256) return 0;
@@ -560,8 +564,8 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_terms(DevPlan<T> d, int
 }
 
 // ------------------------------------------------------------------ I_3
-// One workgroup per (cell, j); loops over the Gauss-Legendre nodes in
-// symmetric pairs (m, m' = M-1-m), rho_m' = -rho_m, w_m' = w_m (the middle
+// One workgroup per (cell, j, group of nodes); loops over the group's
+// Gauss-Legendre nodes in symmetric pairs (m, m' = M-1-m), rho_m' = -rho_m, w_m' = w_m (the middle
 // node of an odd M runs alone).  With s_nu = S w_nu the field shifted by
 // node m (S = inv2(exp(i alpha_jm . b) fwd2(.)) / P^2) and the packed
 // convolutions Phi_a,b = Psi(w_a s_b), Psi = inv2(psi'_j / P^2 fwd2(.)):
@@ -571,7 +575,7 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_terms(DevPlan<T> d, int
 // band stays inside the padded grid; the aliased part of the last product
 // falls outside Xi, which the output keeps.  o' is accumulated as a
 // spectrum, conj(phase) fwd2(sign_a o'_a) with the sign of the B term
-// (-1 for a = 0), packed (0 + i1), (2 + i3), into i3p[cell][j].
+// (-1 for a = 0), packed (0 + i1), (2 + i3), into i3p of the task.
 // c = (pi/J) w_m.  Per pair: 2 shift transforms, 8 packed convolutions of 2
 // transforms each, 2 transforms of the partner sums.
 //
@@ -584,6 +588,9 @@ __global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_terms(DevPlan<T> d, int
 // rounds of long tasks took the time of 3).  More groups would cost launches
 // that fill the chip more than the sums are worth: k_assemble reads the equal
 // of 5 planes per group (four groups: +1.5 % of a collision at N = 32).
+// Float32, and float64 in a workspace without room for the groups, runs one
+// group of all nodes.
+//
 // Planes per task of the shifted-field buffer i3s: the four shifted
 // fields, and in float64 two more for partner sums that do not fit in
 // registers.
@@ -596,7 +603,7 @@ __device__ __forceinline__ T pick4(int i, T a, T b, T c, T d) {
 }
 
 template <typename T, int P, int E, bool PAIR>
-__global__ __launch_bounds__((Fft2<T, P, E>::NT)) __attribute__((amdgpu_waves_per_eu(Kern<T, P, E>::WAVES))) void k_i3(DevPlan<T> d, int ncells) {
+__global__ __launch_bounds__((Fft2<T, P, E>::NT)) void k_i3(DevPlan<T> d, int ncells) {
   using K = Kern<T, P, E, I3Regs<T, P, E>::XB>;
   constexpr unsigned S = sizeof(T);
   constexpr bool SREG = I3Regs<T, P, E>::template sreg<PAIR>();
