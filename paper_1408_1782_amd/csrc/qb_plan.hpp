@@ -169,15 +169,17 @@ constexpr int kTermDirs = 8;
 inline int term_groups(int J, bool one) { return one ? 1 : (J + kTermDirs - 1) / kTermDirs; }
 
 // Cells per launch of k_i3 in chunks of wcells cells.  At most as many as the
-// I_3 buffers of one task per (cell, j) would hold, or 3.8 GB of them: a plan
+// I_3 buffers of one task per (cell, j) would hold, or 7.5 GB of them: a plan
 // of many cells then takes little more than with one group (+15 % at J = 32),
-// where all cells in one launch would take ng times as much.  Up to that, the
-// number that leaves the fewest rounds of resident workgroups partly empty
-// over the launches: 60 cells at N = 32, J = 36, M = 48 take 17.2 ms in one
-// launch, 18.5 in launches of 18 cells (15.2 rounds each).
+// where all cells in one launch would take ng times as much.  (44 cells at
+// N = 32, J = 32, M = 57: 14.0 ms, with 3.8 GB 14.3; 60 cells at N = 64,
+// J = 24, M = 45: 90.5 and 91.4; more than 7.5 GB gains nothing on either.)
+// Up to that, the number that leaves the fewest rounds of resident workgroups
+// partly empty over the launches: 60 cells at N = 32, J = 36, M = 48 take 17.2
+// ms in one launch, 18.5 in launches of 18 cells (15.2 rounds each).
 inline int i3_launch_cells(const qb_problem& p, int wcells, bool one) {
   const int ng = node_groups(p, one), per_cell = p.J * ng;
-  const int tasks = p.N == 16 ? 32768 : p.N == 32 ? 8192 : 2048;
+  const int tasks = p.N == 16 ? 65536 : p.N == 32 ? 16384 : 4096;
   const int most = std::min(wcells, std::max({1, (wcells + ng - 1) / ng, tasks / per_cell}));
   const int resident = p.N == 16 ? 1024 : 256;  // workgroups of the starting tile on the card
   auto rounds = [&](int cells) { return (int64_t)(cells * per_cell + resident - 1) / resident; };

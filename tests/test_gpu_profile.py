@@ -1,6 +1,6 @@
 """GPU test of qb_profile_read's launch counts: one of every kernel class per
 collision launch and two groups of other reverse-mode kernels, however many
-launches the I_3 buffers cut it into (100 cells with J = 40, M = 72: two)."""
+launches the I_3 buffers cut it into (110 cells with J = M = 72: two)."""
 import pytest
 
 import workloads as wl
@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("precision", ["f64", "f32"])
-@pytest.mark.parametrize("J,M,Nx", [(8, 8, 3), (40, 72, 100)])
+@pytest.mark.parametrize("J,M,Nx", [(8, 8, 3), (72, 72, 110)])
 def test_launches_count_once_per_collision(precision, J, M, Nx):
     w = wl.config(2, Nx=Nx, N=16)
     plan = make_plan(w, precision, J, M)

@@ -43,9 +43,9 @@ def test_least_size_is_one_task_per_cell_and_direction(N, J, M):
 @pytest.mark.parametrize("N,J,M", [(16, 32, 16), (32, 32, 32), (32, 40, 71), (64, 32, 64), (64, 40, 71)])
 @pytest.mark.parametrize("Nx", [1, 37, 256, 600])
 def test_preferred_size_stays_near_the_least(N, J, M, Nx):
-    """At most a quarter and 4 GB more in float64, the same in float32."""
+    """At most a quarter and 8 GB more in float64, the same in float32."""
     least, pref = (_bytes(f, N, J, M, Nx) for f in ("qb_workspace_bytes", "qb_workspace_bytes_preferred"))
-    assert least <= pref <= 1.25 * least + 4e9
+    assert least <= pref <= 1.25 * least + 8e9
     assert _bytes("qb_workspace_bytes_preferred", N, J, M, Nx, "f32") == _bytes("qb_workspace_bytes", N, J, M, Nx, "f32")
 
 
@@ -132,17 +132,17 @@ def test_cells_of_every_i3_launch_are_the_same_numbers(monkeypatch, paired, N, J
 
 @pytest.mark.gpu
 def test_more_cells_than_one_i3_launch_in_the_preferred_workspace():
-    """N = 16, J = 40, M = 72 runs I_3 in launches of at most 91 cells: cells of every
-    launch against a plan of one cell and against the oracle."""
+    """N = 16, J = 72, M = 72 runs I_3 in launches of at most 101 cells: cells of
+    every launch against a plan of one cell and against the oracle."""
     import torch
-    N, J, M, Nx = 16, 40, 72, 100
+    N, J, M, Nx = 16, 72, 72, 110
     w, lam = _inputs(N, Nx)
     plan = make_plan(w, "f64", J, M)
     C, G = _run(plan, w, lam)
     plan.close()
-    _check(C, G, N, J, M, Nx, (90, 99))
+    _check(C, G, N, J, M, Nx, (100, 109))
     one = make_plan(w, "f64", J, M, Nx=1)
-    for c in (0, 49, 50, 90, 91, 99):
+    for c in (0, 54, 55, 100, 101, 109):
         W, L = to_dev(w.W0[c : c + 1], "f64"), to_dev(cot_api(lam[c : c + 1]), "f64")
         assert torch.equal(one.collision(W)[0], C[c])
         assert torch.equal(one.collision_vjp(W, L)[0], G[c])
