@@ -49,6 +49,13 @@ def test_preferred_size_stays_near_the_least(N, J, M, Nx):
     assert _bytes("qb_workspace_bytes_preferred", N, J, M, Nx, "f32") == _bytes("qb_workspace_bytes", N, J, M, Nx, "f32")
 
 
+def test_sizes_of_very_many_cells_per_launch():
+    """10^6 cells in one launch: more tasks than 32 bits count."""
+    least, pref = (_bytes(f, 16, 128, 256, 10**6, max_cells=10**6)
+                   for f in ("qb_workspace_bytes", "qb_workspace_bytes_preferred"))
+    assert 10**6 * (46 + 14 * 128) * 32 * 32 * 8 < least <= pref <= 1.25 * least
+
+
 def test_sizes_of_invalid_descriptions_are_zero():
     assert _bytes("qb_workspace_bytes_preferred", 24, 8, 8, 1) == 0
     assert _bytes("qb_workspace_bytes_preferred", 16, 8, 8, 1, max_cells=-1) == 0
