@@ -181,7 +181,7 @@ inline int i3_launch_cells(const qb_problem& p, int wcells, bool one) {
   const int ng = node_groups(p, one), per_cell = p.J * ng;
   const int tasks = p.N == 16 ? 65536 : p.N == 32 ? 16384 : 4096;
   const int most = std::min(wcells, std::max({1, (wcells + ng - 1) / ng, tasks / per_cell}));
-  const int resident = p.N == 16 ? 1024 : 256;  // workgroups of the starting tile on the card
+  const int resident = p.N == 16 ? 1024 : p.N == 32 ? 512 : 256;  // workgroups of the starting tile on the card
   auto rounds = [&](int cells) { return ((int64_t)cells * per_cell + resident - 1) / resident; };
   int best = most;
   int64_t least = INT64_MAX;
