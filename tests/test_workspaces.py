@@ -172,3 +172,18 @@ def test_batch_in_its_least_workspace(monkeypatch):
         b.close()
     for a, c in zip(*out):
         assert rel(a, c) < TOL["f64"]
+
+
+def test_python_takes_the_least_where_memory_is_short(monkeypatch):
+    import torch
+
+    def empty(n, **kw):
+        if n > 1000:
+            raise torch.cuda.OutOfMemoryError("no room")
+        return n
+
+    monkeypatch.setattr(torch, "empty", empty)
+    assert _lib._workspace(900, 500) == 900
+    assert _lib._workspace(5000, 500) == 500
+    with pytest.raises(torch.cuda.OutOfMemoryError):
+        _lib._workspace(5000, 2000)
